@@ -59,29 +59,39 @@ __device__ __forceinline__ float warp_sample(const uint8_t *__restrict__ src, in
     return __builtin_fmaf(ay, bot - top, top);
 }
 
-// warp_sample for a reference region whose samples all map in front of the
-// view and inside [0, sw - 2] x [0, sh - 2] (warp_region_mode): there the
-// reciprocal guard and the border clamps change nothing, so the same
-// operations without them give the same value.  The texel offset is clamped
-// to the image only as a memory guard.
-__device__ __forceinline__ float warp_sample_inside(const uint8_t *__restrict__ src, int sw, int sh, double h0,
-                                                    double h1, double h2, double h3, double h4, double h5, double h6,
-                                                    double h7, double h8, double qx, double qy) {
-    const double hx = __builtin_fma(h0, qx, __builtin_fma(h1, qy, h2));
-    const double hy = __builtin_fma(h3, qx, __builtin_fma(h4, qy, h5));
-    const double hz = __builtin_fma(h6, qx, __builtin_fma(h7, qy, h8));
+// The same sample from a packed view (launch_pack_quads: texel (x, y) and its
+// right, lower and lower-right neighbours, border replicated, in one 32-bit
+// word), split into the word's byte offset with the bilinear fractions and
+// the interpolation, so a kernel can have many of the loads in flight.
+// (hx, hy, hz): the homography applied to the sample point.
+// INSIDE: the reference region maps in front of the view and inside
+// [0, sw - 1] x [0, sh - 1] (warp_region_inside): there the reciprocal guard
+// and the border clamps change nothing, so the same operations without them
+// give the same value.
+struct QuadSample {
+    uint32_t offset;
+    float ax, ay;
+};
+template <bool INSIDE>
+__device__ __forceinline__ QuadSample warp_quad(int sw, int sh, double hx, double hy, double hz) {
     const double r = recip(hz);
-    const double sx = __builtin_fma(hx, r, -0.5);
-    const double sy = __builtin_fma(hy, r, -0.5);
+    const double inv = INSIDE || hz > 1e-300 ? r : 0.0;
+    double sx = __builtin_fma(hx, inv, -0.5);
+    double sy = __builtin_fma(hy, inv, -0.5);
+    if (!INSIDE) {
+        sx = __builtin_fmin(__builtin_fmax(sx, 0.0), (double)(sw - 1));
+        sy = __builtin_fmin(__builtin_fmax(sy, 0.0), (double)(sh - 1));
+    }
     const uint32_t xa = (uint32_t)(int)sx, ya = (uint32_t)(int)sy;
-    const float ax = (float)__builtin_amdgcn_fract(sx);
-    const float ay = (float)__builtin_amdgcn_fract(sy);
-    const uint32_t b0 = min(__umul24(ya, (uint32_t)sw) + xa, (uint32_t)(sw * (sh - 1) - 2));
-    const uint32_t b1 = b0 + (uint32_t)sw;
-    const float i00 = (float)src[b0];
-    const float i10 = (float)src[b0 + 1u];
-    const float i01 = (float)src[b1];
-    const float i11 = (float)src[b1 + 1u];
+    QuadSample q;
+    q.ax = (float)__builtin_amdgcn_fract(sx);
+    q.ay = (float)__builtin_amdgcn_fract(sy);
+    q.offset = (__umul24(ya, (uint32_t)sw) + xa) << 2;
+    return q;
+}
+__device__ __forceinline__ float quad_value(uint32_t t, float ax, float ay) {
+    const float i00 = (float)(t & 0xFFu), i10 = (float)((t >> 8) & 0xFFu), i01 = (float)((t >> 16) & 0xFFu),
+                i11 = (float)(t >> 24);
     const float top = __builtin_fmaf(ax, i10 - i00, i00);
     const float bot = __builtin_fmaf(ax, i11 - i01, i01);
     return __builtin_fmaf(ay, bot - top, top);
@@ -91,15 +101,19 @@ __device__ __forceinline__ float warp_sample_inside(const uint8_t *__restrict__ 
 // x (qy_lo..qy_hi) maps in front of the view and inside [0, sw - 2] x
 // [0, sh - 2] (with a 1e-6 px margin for rounding): hz is affine, so a
 // region in front of the view maps to the convex quadrilateral of its
-// corners' images.  corner selects the corner (bit 0: x, bit 1: y).
-__device__ __forceinline__ bool warp_corner_inside(const double *H, int corner, double qx_lo, double qx_hi,
-                                                   double qy_lo, double qy_hi, int sw, int sh) {
-    const double qx = (corner & 1) ? qx_hi : qx_lo, qy = (corner & 2) ? qy_hi : qy_lo;
-    const double hz = H[6] * qx + H[7] * qy + H[8];
-    if (!(hz > 1e-200)) return false;
-    const double X = (H[0] * qx + H[1] * qy + H[2]) / hz - 0.5;
-    const double Y = (H[3] * qx + H[4] * qy + H[5]) / hz - 0.5;
-    return X >= 1e-6 && X <= (double)(sw - 2) - 1e-6 && Y >= 1e-6 && Y <= (double)(sh - 2) - 1e-6;
+// corners' images.
+__device__ __forceinline__ bool warp_region_inside(const double *H, double qx_lo, double qx_hi, double qy_lo,
+                                                   double qy_hi, int sw, int sh) {
+    const double lo = 0.5 + 1e-6, hx = (double)(sw - 2) + 0.5 - 1e-6, hy = (double)(sh - 2) + 0.5 - 1e-6;
+    bool in = true;
+    for (int corner = 0; corner < 4; ++corner) {
+        const double qx = (corner & 1) ? qx_hi : qx_lo, qy = (corner & 2) ? qy_hi : qy_lo;
+        const double hz = H[6] * qx + H[7] * qy + H[8];
+        const double X = H[0] * qx + H[1] * qy + H[2], Y = H[3] * qx + H[4] * qy + H[5];
+        // X / hz - 0.5 against the bounds, without the division
+        in = in && hz > 1e-200 && X >= lo * hz && X <= hx * hz && Y >= lo * hz && Y <= hy * hz;
+    }
+    return in;
 }
 
 // Minimum over the 64 lanes of a wavefront: DPP within each row of 16
@@ -121,6 +135,10 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     v = dpp_min_step<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
     v = dpp_min_step<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+__device__ __forceinline__ int wave_min_i32(int v) {
+    return (int)(wave_min_u32((uint32_t)v ^ 0x80000000u) ^ 0x80000000u);
 }
 
 __device__ __forceinline__ void ray_of(const double *Ki, double u, double v, double r[3]) {

@@ -46,6 +46,26 @@ hipError_t launch_pyr_down(const uint8_t *src, int w, int h, int stride, uint8_t
     return hipGetLastError();
 }
 
+// --------------------------------------------------------------- packed texels
+// The sweep's bilinear samples read their four texels with one aligned 32-bit
+// load from this form instead of four byte loads from the image.
+__global__ __launch_bounds__(256) void k_pack_quads(const QuadArgs a) {
+    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
+    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
+    if (x >= a.w || y >= a.h) return;
+    const uint8_t *__restrict__ src = a.src[blockIdx.z];
+    const int xb = min(x + 1, a.w - 1), yb = min(y + 1, a.h - 1);
+    const uint8_t *ra = src + (size_t)y * a.w, *rb = src + (size_t)yb * a.w;
+    a.dst[blockIdx.z][(size_t)y * a.w + x] =
+        (uint32_t)ra[x] | (uint32_t)ra[xb] << 8 | (uint32_t)rb[x] << 16 | (uint32_t)rb[xb] << 24;
+}
+
+hipError_t launch_pack_quads(const QuadArgs &a, int n, hipStream_t s) {
+    dim3 grid((a.w + 63) / 64, (a.h + 3) / 4, n);
+    hipLaunchKernelGGL(k_pack_quads, grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 // --------------------------------------------------------------- census
 // Census transform of the reference level (Alg. 1 cost function): bit
 // (nbits-1-b) = [I(q_b) < I(p)], q_b the b-th window position in row-major

@@ -4,6 +4,8 @@
 // unit.
 #include "kernels.hpp"
 
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 
@@ -17,27 +19,32 @@ template <int CW, int CH, int COST>
 hipError_t sweep_launch_batch_cfg(const SweepArgs *list, const int *prefix, int n, int blocks, int rpt,
                                   hipStream_t s);
 
-// Rows per thread (tile height / 4): 8 halves the halo and the LDS reads per
-// pixel, 4 keeps more waves resident (the NCC's double-precision window
-// sums take many registers: 4 unless asked otherwise).
+// Tile height / 4 (one wavefront per 4 rows): 8 halves the halo of 4, 4 gives
+// more workgroups and smaller unions of label windows.
 int sweep_rpt(const SweepArgs &a) {
     return a.rows_per_thread == 4 ? 4 : (a.rows_per_thread == 8 ? 8 : (a.cost == 1 ? 4 : 8));
 }
 
-// Tile grid of one frame for rpt rows per thread; returns the tile count.
+// Tile grid of one frame for tiles of 4 * rpt rows; returns the tile count.
 int sweep_tiles(SweepArgs &a, int rpt) {
     a.tiles_x = (a.w + kSweepTileW - 1) / kSweepTileW;
     a.tiles_y = (a.h + 4 * rpt - 1) / (4 * rpt);
     return a.tiles_x * a.tiles_y;
 }
 
-// Split each tile's label range into chunks until there are about `target`
-// workgroups: a tile's whole label loop is long (hundreds of labels x
-// views), so with few workgroups the last round leaves CUs idle.
-int sweep_chunks(const SweepArgs &a, int tiles, int target) {
-    int want = (target + tiles - 1) / tiles;
-    int maxc = (a.D + 7) / 8;
-    return want < 1 ? 1 : (want > maxc ? maxc : want);
+// Split each tile's label range into chunks (workgroups of their own): a
+// tile's whole label loop is long, and with few workgroups the last round
+// leaves CUs idle.  `waves` wavefronts over all tiles are wanted where chunks
+// keep 16 labels (shorter ones repeat the setup and write S in pieces), half
+// as many down to 4 labels a chunk.  Measured: 1280x720 x 64 labels, level 0:
+// 0.80 ms with 4 chunks of 16, 0.90 ms with 16 of 4; 480x270 x 128 labels:
+// 0.37 ms with 8 chunks, 0.35 ms with 31; 333x187 x 16 labels, three levels:
+// 0.38 ms with chunks of at least 8, 0.24 ms of at least 4.
+int sweep_chunks(const SweepArgs &a, int tiles, int rpt, double waves) {
+    const double per_chunk = (double)tiles * rpt;
+    const int most = std::max(1, a.D / 16), least = std::max(1, (a.D + 3) / 4);
+    const int full = (int)std::min(std::ceil(waves / per_chunk), 1e6), half = (int)std::min(std::ceil(0.5 * waves / per_chunk), 1e6);
+    return std::max(1, std::max(std::min(full, most), std::min(half, least)));
 }
 
 hipError_t launch_sweep(const SweepArgs &a0, hipStream_t s) {
@@ -46,13 +53,11 @@ hipError_t launch_sweep(const SweepArgs &a0, hipStream_t s) {
     const int tiles = sweep_tiles(a, rpt);
     if (tiles == 0) return hipSuccess;
     if (a.n_chunks <= 0) {
-        // about 8192 workgroups (32 per CU) measured best at 1080p x 128
-        // labels and 2704x1520 x 384 labels (2048: 2 % / 28 % slower); more
-        // chunks repeat the per-workgroup setup.  FASSMVS_SWEEP_BLOCKS
-        // overrides the target.
+        // 32768 wavefronts are eight rounds of the 16 a CU holds.
+        // FASSMVS_SWEEP_BLOCKS asks for that many workgroups instead.
         const char *e = std::getenv("FASSMVS_SWEEP_BLOCKS");
-        const int target = e && std::atoi(e) > 0 ? std::atoi(e) : 8192;
-        a.n_chunks = sweep_chunks(a, tiles, target);
+        const int target = e ? std::atoi(e) : 0;
+        a.n_chunks = sweep_chunks(a, tiles, rpt, target > 0 ? (double)target * rpt : 32768.0);
     }
     dim3 grid((unsigned)(tiles * a.n_chunks));
     // (window, cost) pairs the sweep is built for
@@ -74,7 +79,7 @@ hipError_t launch_sweep(const SweepArgs &a0, hipStream_t s) {
 // captured in a graph apart from the argument upload.
 // prepare_sweep_batch: host[0..n-1] are the frames' args (same window and
 // cost, no pre-warped input); their tile grids and chunk counts are set
-// (about `target` workgroups over all frames, each frame's share by its
+// (about 4 * `target` wavefronts over all frames, each frame's share by its
 // pixels x labels) and they are written with the workgroup prefix (n + 1
 // ints) to out (host memory of sweep_batch_bytes(n)).  Returns the
 // workgroup count, or -1 if the frames cannot share a launch.
@@ -92,7 +97,7 @@ int prepare_sweep_batch(SweepArgs *host, int n, int rpt, int target, void *out) 
         a.rows_per_thread = rpt;
         const int tiles = sweep_tiles(a, rpt);
         const double share = work > 0.0 ? (double)a.w * a.h * a.D / work : 1.0;
-        a.n_chunks = sweep_chunks(a, tiles, (int)(target * share + 0.5));
+        a.n_chunks = sweep_chunks(a, tiles, rpt, 4.0 * target * share);
         prefix[i + 1] = prefix[i] + tiles * a.n_chunks;
     }
     std::memcpy(out, host, sizeof(SweepArgs) * n);

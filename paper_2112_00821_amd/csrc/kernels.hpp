@@ -28,7 +28,7 @@ struct SweepArgs {
     int w, h;                 // reference level size (views have the same size)
     int cw, ch;               // census window
     int n_views, nL, nR, m;
-    const uint8_t *views[kMaxViews];
+    const uint32_t *quads[kMaxViews];   // [h][w] packed 2x2 texels of each view (launch_pack_quads)
     int side[kMaxViews];
     int cost;                 // 0: census-Hamming, 1: NCC
     const uint64_t *ct_ref;   // [h][w] reference census (census cost)
@@ -91,6 +91,15 @@ hipError_t launch_sum_u16(const uint16_t *const *bufs, int n, size_t count, uint
 
 // ---------------------------------------------------------------- image stages
 hipError_t launch_pyr_down(const uint8_t *src, int w, int h, int stride, uint8_t *dst, hipStream_t s);
+// Packed 2x2 texels of n views: dst[k][y][x] holds texel (x, y), its right,
+// its lower and its lower-right neighbour (lowest byte first), the border
+// replicated.
+struct QuadArgs {
+    int w, h;
+    const uint8_t *src[kMaxViews];
+    uint32_t *dst[kMaxViews];
+};
+hipError_t launch_pack_quads(const QuadArgs &a, int n, hipStream_t s);
 hipError_t launch_census(const uint8_t *img, int w, int h, int cw, int ch, uint64_t *out, hipStream_t s);
 hipError_t launch_warp(const uint8_t *src, int sw, int sh, const double *dH, int rw, int rh, float *out,
                        hipStream_t s);

@@ -946,6 +946,33 @@ const uint8_t *level_ref(fassmvs_handle *h, const FramePlan &P, int l) {
     return (const uint8_t *)h->pyr[0].p + level_offset(P, l);
 }
 
+// Where the packed texels of view k sit while level l is swept: in the
+// level's own map buffers, which are written only after its aggregation
+// (3 + 3 + 1 + 1 views of 4 bytes a pixel fill the raw and smoothed normals
+// and the two depth maps), so a frame holds no memory for them.
+uint32_t *level_quads(fassmvs_handle *h, const FramePlan &P, int l, int k) {
+    auto &B = h->lb[l];
+    const size_t N = (size_t)P.lv[l].w * P.lv[l].h;
+    if (k < 3) return (uint32_t *)B.nraw.p + N * k;
+    if (k < 6) return (uint32_t *)B.normal.p + N * (k - 3);
+    return (uint32_t *)(k == 6 ? B.depth_raw.p : B.depth.p);
+}
+
+fassmvs_status enqueue_quads(fassmvs_handle *h, const FramePlan &P, int l) {
+    const LevelPlan &L = P.lv[l];
+    Timer t(h, ST_PYR);
+    QuadArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.w = L.w;
+    a.h = L.h;
+    for (int k = 0; k < P.n_views; ++k) {
+        a.src[k] = (const uint8_t *)h->pyr[k + 1].p + level_offset(P, l);
+        a.dst[k] = level_quads(h, P, l, k);
+    }
+    HIPCHK(h, launch_pack_quads(a, P.n_views, h->stream), "view packing");
+    return FASSMVS_OK;
+}
+
 fassmvs_status enqueue_census(fassmvs_handle *h, const FramePlan &P, int l) {
     const fassmvs_config &c = h->cfg;
     if (c.cost != 0) return FASSMVS_OK;
@@ -959,7 +986,6 @@ fassmvs_status enqueue_census(fassmvs_handle *h, const FramePlan &P, int l) {
 SweepArgs sweep_args(fassmvs_handle *h, const FramePlan &P, int l) {
     const fassmvs_config &c = h->cfg;
     const LevelPlan &L = P.lv[l];
-    const size_t off = level_offset(P, l);
     SweepArgs a;
     std::memset(&a, 0, sizeof(a));
     a.w = L.w;
@@ -971,7 +997,7 @@ SweepArgs sweep_args(fassmvs_handle *h, const FramePlan &P, int l) {
     a.nR = P.nR;
     a.m = P.m;
     for (int k = 0; k < P.n_views; ++k) {
-        a.views[k] = (const uint8_t *)h->pyr[k + 1].p + off;
+        a.quads[k] = level_quads(h, P, l, k);
         a.side[k] = P.side[k];
     }
     a.cost = c.cost;
@@ -991,14 +1017,13 @@ SweepArgs sweep_args(fassmvs_handle *h, const FramePlan &P, int l) {
     a.S = (uint8_t *)h->S.p;
     a.work = (unsigned long long *)h->work_ctr.p;
     // Tile height for the census cost (FASSMVS_SWEEP_ROWS overrides): 64x16
-    // tiles where several plane families share the level (each family's
-    // label windows move across a tile, and a shorter tile evaluates a
-    // smaller union of them; it also keeps 4 waves per SIMD resident) or
-    // where the level is small (more tiles to spread over the CUs); 64x32
-    // otherwise (less halo to warp).  The same costs either way.
+    // tiles where the level is small (more workgroups, smaller unions of
+    // label windows), 64x32 otherwise (fewer halo samples: 1.5 against 1.75
+    // per pixel).  Measured: 640x480 x 168 labels 0.62 ms with 16 rows, 0.67
+    // ms with 32; 960x540 x 128 labels the same; 1920x1080 x 128 labels 5.22
+    // and 4.96 ms.  The same costs either way.
     int rows = sweep_rows();
-    if (rows == 0 && c.cost == 0)
-        rows = (L.F > 1 || (double)L.w * L.h * L.D <= 33554432.0) ? 4 : 8;
+    if (rows == 0 && c.cost == 0) rows = (double)L.w * L.h * L.D <= 67108864.0 ? 4 : 8;
     a.rows_per_thread = rows;
     return a;
 }
@@ -1183,6 +1208,7 @@ fassmvs_status enqueue_frame(fassmvs_handle *h, const FramePlan &P) {
     for (int l = P.n_levels - 1; l >= 0; --l) {
         const LevelPlan &L = P.lv[l];
         h->cur_level = l;
+        if ((st = enqueue_quads(h, P, l)) != FASSMVS_OK) return st;
         if ((st = enqueue_census(h, P, l)) != FASSMVS_OK) return st;
         {
             Timer t(h, ST_SWEEP);
@@ -1526,6 +1552,7 @@ fassmvs_status batch_enqueue_group(fassmvs_handle *h, const BatchGroup &g, hipSt
         const int m = (int)br.frames.size();
         for (int j = 0; j < m; ++j) {
             fassmvs_handle *ch = h->children[br.frames[j]];
+            if ((st = enqueue_quads(ch, ch->plan, br.levels[j])) != FASSMVS_OK) return fail(h, st, ch->err);
             if ((st = enqueue_census(ch, ch->plan, br.levels[j])) != FASSMVS_OK) return fail(h, st, ch->err);
         }
         for (const SweepLaunch &S : br.sweeps)
@@ -2529,7 +2556,6 @@ fassmvs_status stage_cost_any(fassmvs_handle *h, int cost, int32_t w, int32_t hg
     for (int k = 0; k < n_views; ++k) {
         if (!views[k] && !warped) return fail(h, FASSMVS_EINVAL, "null view");
         if (view_side[k] != -1 && view_side[k] != 1) return fail(h, FASSMVS_EINVAL, "view_side must be -1 or +1");
-        a.views[k] = views[k];
         a.side[k] = view_side[k];
         if (view_side[k] < 0) a.nL++; else a.nR++;
     }
@@ -2558,7 +2584,29 @@ fassmvs_status stage_cost_any(fassmvs_handle *h, int cost, int32_t w, int32_t hg
     a.warped = warped;
     a.S = S;
     a.rows_per_thread = sweep_rows();
-    hipError_t e = launch_sweep(a, h->stream);
+    hipError_t e = hipSuccess;
+    uint32_t *quads = nullptr;   // the views' packed texels, held for this call only
+    if (!warped) {
+        if ((e = hipMalloc((void **)&quads, (size_t)n_views * w * hgt * 4)) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(h, FASSMVS_ENOMEM, std::string("device allocation failed: ") + hipGetErrorString(e));
+        }
+        QuadArgs q;
+        std::memset(&q, 0, sizeof(q));
+        q.w = w;
+        q.h = hgt;
+        for (int k = 0; k < n_views; ++k) {
+            q.src[k] = views[k];
+            a.quads[k] = q.dst[k] = quads + (size_t)k * w * hgt;
+        }
+        e = launch_pack_quads(q, n_views, h->stream);
+    }
+    if (e == hipSuccess) e = launch_sweep(a, h->stream);
+    if (quads) {
+        const hipError_t es = hipStreamSynchronize(h->stream);
+        hipFree(quads);
+        if (e == hipSuccess) e = es;
+    }
     if (e == hipErrorInvalidValue) return fail(h, FASSMVS_EUNSUPPORTED, "matching window not built");
     HIPCHK(h, e, "sweep launch");
     return FASSMVS_OK;
