@@ -20,6 +20,7 @@
 #include "../../include/fassmvs.h"
 #include "kernels.hpp"
 #include "handle_internal.hpp"
+#include "host_mover.hpp"
 
 using namespace fmvs;
 
@@ -173,6 +174,7 @@ struct fassmvs_handle {
     // pinned staging
     void *pin = nullptr;
     size_t pin_bytes = 0;
+    HostMover mover;   // maps to host memory, images into the staging
 
     // timers
     std::vector<TimedEvent> pending_timers;
@@ -1173,19 +1175,29 @@ fassmvs_status enqueue_post(fassmvs_handle *h, const FramePlan &P, int l) {
 
 // Images to level 0 of each pyramid and the parameter blob to the device,
 // through the handle's pinned staging (host images) or device copies.
-fassmvs_status upload_frame(fassmvs_handle *h, const FramePlan &P, const fassmvs_image *ref,
+fassmvs_status upload_frame(fassmvs_handle *h, HostMover &mover, const FramePlan &P, const fassmvs_image *ref,
                             const fassmvs_image *views, int mem_kind) {
     fassmvs_status wst = weight_table(h, h->cfg.normal_radius, h->cfg.normal_beta);
     if (wst != FASSMVS_OK) return wst;
     const size_t N0 = (size_t)P.w * P.h;
     Timer t(h, ST_UPLOAD);
     uint8_t *pin = (uint8_t *)h->pin;
+    if (mem_kind == FASSMVS_MEM_HOST) {
+        std::vector<HostPiece> pieces;
+        const size_t band = std::max<size_t>(1, HostMover::kPiece / P.w);   // rows of a piece
+        for (int i = 0; i <= P.n_views; ++i) {
+            const fassmvs_image &im = i == 0 ? *ref : views[i - 1];
+            for (size_t y = 0; y < (size_t)P.h; y += band)
+                pieces.push_back({pin + N0 * i + y * P.w, im.pixels + y * im.stride, (size_t)P.w,
+                                  std::min(band, P.h - y), (size_t)P.w, (size_t)im.stride});
+        }
+        mover.copy(pieces);
+    }
     for (int i = 0; i <= P.n_views; ++i) {
         const fassmvs_image &im = i == 0 ? *ref : views[i - 1];
         uint8_t *dst = (uint8_t *)h->pyr[i].p;
         if (mem_kind == FASSMVS_MEM_HOST) {
             uint8_t *stg = pin + N0 * i;
-            for (int y = 0; y < P.h; ++y) std::memcpy(stg + (size_t)y * P.w, im.pixels + (size_t)y * im.stride, P.w);
             HIPCHK(h, hipMemcpyAsync(dst, stg, N0, hipMemcpyHostToDevice, h->stream), "image upload");
         } else if (h->prebuilt) {
             HIPCHK(h, hipMemcpyAsync(dst, im.pixels, level_offset(P, P.n_levels), hipMemcpyDeviceToDevice, h->stream),
@@ -1323,10 +1335,21 @@ fassmvs_status enqueue_frame_graph(fassmvs_handle *h, const FramePlan &P) {
     return FASSMVS_OK;
 }
 
-fassmvs_status copy_out(fassmvs_handle *h, void *dst, const void *src, size_t bytes, int mem_kind) {
-    if (!dst) return FASSMVS_OK;
-    hipMemcpyKind k = mem_kind == FASSMVS_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    HIPCHK(h, hipMemcpyAsync(dst, src, bytes, k, h->stream), "output copy");
+// A finished frame's level-0 maps of N pixels (held by `from`) to the
+// caller's buffers (NULL: not wanted), complete when this returns.
+fassmvs_status copy_maps(fassmvs_handle *h, fassmvs_handle *from, size_t N, float *depth, float *normal, float *conf,
+                         int mem_kind) {
+    const auto &B = from->lb[0];
+    std::vector<DeviceRange> maps;
+    if (depth) maps.push_back({depth, B.depth.p, N * 4});
+    if (normal) maps.push_back({normal, B.normal.p, N * 12});
+    if (conf) maps.push_back({conf, B.conf.p, N * 4});
+    if (mem_kind == FASSMVS_MEM_HOST) {
+        HIPCHK(h, h->mover.to_host(maps, h->stream), "output copy");
+    } else {
+        for (auto &m : maps)
+            HIPCHK(h, hipMemcpyAsync(m.dst, m.src, m.bytes, hipMemcpyDeviceToDevice, h->stream), "output copy");
+    }
     return FASSMVS_OK;
 }
 
@@ -1659,7 +1682,7 @@ fassmvs_status submit_frame_locked(fassmvs_handle *h, const fassmvs_image *ref, 
         if (h->frame_t0) HIPCHK(h, hipEventRecord(h->frame_t0, h->stream), "frame start event");
     }
     h->cur_level = -1;
-    if ((st = upload_frame(h, P, ref, views, mem_kind)) != FASSMVS_OK) return st;
+    if ((st = upload_frame(h, h->mover, P, ref, views, mem_kind)) != FASSMVS_OK) return st;
     if ((st = enqueue_frame_graph(h, P)) != FASSMVS_OK) return st;
     HIPCHK(h, hipMemcpyAsync(h->work_host, h->work_ctr.p, 8, hipMemcpyDeviceToHost, h->stream), "work counter");
     HIPCHK(h, hipEventRecord(h->done, h->stream), "event record");
@@ -1940,7 +1963,7 @@ fassmvs_status fassmvs_submit_batch(fassmvs_handle *h, const fassmvs_frame *fram
         const fassmvs_frame &fr = frames[i];
         fassmvs_handle *ch = h->children[i];
         ch->stream = h->stream;
-        if ((st = upload_frame(ch, ch->plan, fr.ref, fr.views, mem_kind)) != FASSMVS_OK) return fail(h, st, ch->err);
+        if ((st = upload_frame(ch, h->mover, ch->plan, fr.ref, fr.views, mem_kind)) != FASSMVS_OK) return fail(h, st, ch->err);
     }
     // One run of the batch with tuning t, from a captured graph or launch by
     // launch; with ms, timed (HIP events on the handle's stream).
@@ -2093,12 +2116,9 @@ fassmvs_status fassmvs_poll_batch(fassmvs_handle *h, uint64_t ticket, int32_t in
         h->batch_busy = false;
     }
     fassmvs_handle *ch = h->children[index];
-    const size_t N0 = (size_t)ch->plan.w * ch->plan.h;
-    auto &B = ch->lb[0];
-    fassmvs_status st;
-    if ((st = copy_out(h, depth, B.depth.p, N0 * 4, mem_kind)) != FASSMVS_OK) return st;
-    if ((st = copy_out(h, normal, B.normal.p, N0 * 12, mem_kind)) != FASSMVS_OK) return st;
-    if ((st = copy_out(h, confidence, B.conf.p, N0 * 4, mem_kind)) != FASSMVS_OK) return st;
+    const fassmvs_status st =
+        copy_maps(h, ch, (size_t)ch->plan.w * ch->plan.h, depth, normal, confidence, mem_kind);
+    if (st != FASSMVS_OK) return st;
     HIPCHK(h, hipStreamSynchronize(h->stream), "output copy");
     return FASSMVS_OK;
 }
@@ -2244,14 +2264,11 @@ fassmvs_status fassmvs_poll(fassmvs_handle *h, uint64_t ticket, float *depth, fl
         if (el >= wait_ms) return FASSMVS_PENDING;
         std::this_thread::sleep_for(std::chrono::microseconds(200));
     }
-    const size_t N0 = (size_t)h->out_w * h->out_h;
-    auto &B = h->lb[0];
-    fassmvs_status st;
     {
         Timer t(h, ST_OUTPUT);
-        if ((st = copy_out(h, depth, B.depth.p, N0 * 4, mem_kind)) != FASSMVS_OK) return st;
-        if ((st = copy_out(h, normal, B.normal.p, N0 * 12, mem_kind)) != FASSMVS_OK) return st;
-        if ((st = copy_out(h, confidence, B.conf.p, N0 * 4, mem_kind)) != FASSMVS_OK) return st;
+        const fassmvs_status st =
+            copy_maps(h, h, (size_t)h->out_w * h->out_h, depth, normal, confidence, mem_kind);
+        if (st != FASSMVS_OK) return st;
     }
     HIPCHK(h, hipStreamSynchronize(h->stream), "output copy");
     collect_timers(h);
@@ -2469,6 +2486,8 @@ fassmvs_status fassmvs_memcpy(fassmvs_handle *h, void *dst, const void *src, siz
         hipLaunchKernelGGL(k_copy16, dim3(2048), dim3(256), 0, h->stream, (uint4 *)dst, (const uint4 *)src,
                            bytes / 16);
         HIPCHK(h, hipGetLastError(), "copy launch");
+    } else if (kind == 1 && bytes >= ((size_t)1 << 20)) {
+        HIPCHK(h, h->mover.to_host({{dst, src, bytes}}, h->stream), "copy");
     } else {
         HIPCHK(h, hipMemcpyAsync(dst, src, bytes, k[kind], h->stream), "copy");
     }

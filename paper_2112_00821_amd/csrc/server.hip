@@ -31,6 +31,7 @@
 
 #include "../../include/fassmvs.h"
 #include "handle_internal.hpp"
+#include "host_mover.hpp"
 
 using fmvs::handle_growth;
 using fmvs::handle_held;
@@ -191,6 +192,7 @@ struct fassmvs_server {
     bool reserve_pending = false;   // a stream opened: size the slots for it when the device is idle
     hipStream_t upload = nullptr, fetch = nullptr;   // non-blocking streams for image uploads and result copies
     std::mutex fetch_mu;
+    fmvs::HostMover mover;   // results to host memory, under fetch_mu
 };
 
 namespace {
@@ -609,15 +611,22 @@ fassmvs_status fassmvs_server_fetch(fassmvs_server *s, uint64_t request_id, floa
         s->fetched_pending.erase(it);
     }
     const size_t N = (size_t)r.info.width * r.info.height;
-    const hipMemcpyKind kind = mem_kind == FASSMVS_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
     // copies on the server's own non-blocking stream: they wait for nothing
     // but themselves, frames in flight keep running
     std::lock_guard<std::mutex> flk(s->fetch_mu);
+    std::vector<fmvs::DeviceRange> maps;
+    if (depth) maps.push_back({depth, r.depth, N * 4});
+    if (normal) maps.push_back({normal, r.normal, N * 12});
+    if (confidence) maps.push_back({confidence, r.conf, N * 4});
     hipError_t e = hipSuccess;
-    if (depth && e == hipSuccess) e = hipMemcpyAsync(depth, r.depth, N * 4, kind, s->fetch);
-    if (normal && e == hipSuccess) e = hipMemcpyAsync(normal, r.normal, N * 12, kind, s->fetch);
-    if (confidence && e == hipSuccess) e = hipMemcpyAsync(confidence, r.conf, N * 4, kind, s->fetch);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->fetch);
+    if (mem_kind == FASSMVS_MEM_HOST) {
+        e = hipSetDevice(s->cfg.device);
+        if (e == hipSuccess) e = s->mover.to_host(maps, s->fetch);
+    } else {
+        for (auto &m : maps)
+            if (e == hipSuccess) e = hipMemcpyAsync(m.dst, m.src, m.bytes, hipMemcpyDeviceToDevice, s->fetch);
+        if (e == hipSuccess) e = hipStreamSynchronize(s->fetch);
+    }
     give_maps(r);
     return e == hipSuccess ? FASSMVS_OK : sfail(s, FASSMVS_EDEVICE, "result copy failed");
 }
