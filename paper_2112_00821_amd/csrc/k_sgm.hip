@@ -31,53 +31,38 @@ int sgm_paths(int dir, int w, int h) {
     return w + h - 1;
 }
 
-// Winner-takes-all over the summed path costs (Eq. sgm-aggr, sgm-wta): one
-// wavefront per pixel, labels across lanes; the packed (cost << 16 | label)
+// Winner-takes-all over the summed path costs (Eq. sgm-aggr, sgm-wta) of
+// fewer than 8 labels: one thread per pixel.  The packed (cost << 16 | label)
 // minimum gives the smallest label on ties.  Also records the aggregate at
 // the winner's two neighbours inside its family window for the refinement.
-template <int K>
-__global__ __launch_bounds__(256) void k_wta(const SgmArgs a) {
-    const int lane = threadIdx.x & 63;
+__global__ __launch_bounds__(256) void k_wta_few(const SgmArgs a) {
     const size_t N = (size_t)a.w * a.h;
+    const size_t p = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (p >= N) return;
     const int D = a.D;
-    const size_t waves = (size_t)gridDim.x * 4;
-    for (size_t p = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); p < N; p += waves) {
-        uint32_t tot[K];
-        uint32_t key = 0xFFFFFFFFu;
+    uint32_t tot[7], key = 0xFFFFFFFFu;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int i = k * 64 + lane;
-            uint32_t s = 0;
-            if (i < D) {
-#pragma unroll
-                for (int b = 0; b < 8; ++b)
-                    if (b < a.n_in) s += a.in[b][p * D + i];
-                uint32_t kk = (s << 16) | (uint32_t)i;
-                key = kk < key ? kk : key;
-            }
-            tot[k] = s;
-        }
-        key = wave_min_u32(key);
-        const int best = (int)(key & 0xFFFFu);
-        int f = 0;
-        while (f + 1 < a.n_fam && best >= a.foff[f + 1]) ++f;
-        const int l = best - a.foff[f];
-        uint32_t cm = 0xFFFF, cp = 0xFFFF;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int i = k * 64 + lane;
-            if (l >= 1 && i == best - 1) cm = tot[k];
-            if (l + 1 < a.W[f] && i == best + 1) cp = tot[k];
-        }
-        cm = wave_min_u32(cm);
-        cp = wave_min_u32(cp);
-        if (lane == 0) {
-            a.wta[p] = (uint16_t)best;
-            a.c3[3 * p] = (uint16_t)cm;
-            a.c3[3 * p + 1] = (uint16_t)(key >> 16);
-            a.c3[3 * p + 2] = (uint16_t)cp;
-        }
+    for (int i = 0; i < 7; ++i) {
+        tot[i] = 0;
+        if (i >= D) continue;
+        for (int b = 0; b < a.n_in; ++b) tot[i] += a.in[b][p * D + i];
+        const uint32_t k = (tot[i] << 16) | (uint32_t)i;
+        key = k < key ? k : key;
     }
+    const int best = (int)(key & 0xFFFFu);
+    int f = 0;
+    while (f + 1 < a.n_fam && best >= a.foff[f + 1]) ++f;
+    const int l = best - a.foff[f];
+    uint32_t cm = 0xFFFF, cp = 0xFFFF;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) {
+        if (l >= 1 && i == best - 1) cm = tot[i];
+        if (l + 1 < a.W[f] && i == best + 1) cp = tot[i];
+    }
+    a.wta[p] = (uint16_t)best;
+    a.c3[3 * p] = (uint16_t)cm;
+    a.c3[3 * p + 1] = (uint16_t)(key >> 16);
+    a.c3[3 * p + 2] = (uint16_t)cp;
 }
 
 // Row-level (16-lane) minimum: every lane of a DPP row ends with its row's
@@ -96,19 +81,24 @@ __device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {
 
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 
-// Winner-takes-all for label counts that are a multiple of 8: a DPP row of
-// 16 lanes owns one pixel (4 pixels per wavefront, contiguous in memory);
-// each lane reads 8 labels of every direction buffer with one 16-byte load
-// and adds them as packed 16-bit pairs (the aggregate fits 16 bits by the
-// configuration's bound); argmin and the neighbours' aggregates come from
-// row-level DPP reductions.
-template <int NCH>
+// Winner-takes-all from 8 labels on: a DPP row of 16 lanes owns one pixel (4
+// pixels per wavefront, contiguous in memory); each lane reads 8 labels of
+// every direction buffer with one 16-byte load and adds them as packed 16-bit
+// pairs (the aggregate fits 16 bits by the configuration's bound); argmin and
+// the neighbours' aggregates come from row-level DPP reductions.  Bound by
+// the path costs' bytes (6.3 TB/s at 1920x1080 x 128 labels).  Where the
+// label count is no multiple of 8 the last chunk starts 8 before the end, so
+// that every load stays inside its pixel: the labels it repeats have the same
+// sums.  Rows then start at 2-byte steps and loads are not aligned: 641x479 x
+// 97 labels 0.26 ms with one label a lane, 0.10 ms so.
+typedef unsigned short ushort8_t __attribute__((ext_vector_type(8), aligned(2)));
+template <int NCH, bool ALIGNED>
 __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
     const int lane = threadIdx.x & 63;
     const int row = lane >> 4, l16 = lane & 15;
     const size_t N = (size_t)a.w * a.h;
     const int D = a.D;
-    const int nch = D >> 3;
+    const int nch = (D + 7) >> 3;
     const size_t waves = (size_t)gridDim.x * 4;
     const size_t wid = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const size_t vol_bytes = N * D * 2;
@@ -122,6 +112,7 @@ __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
         for (int j = 0; j < NCH; ++j) {
             const int c = l16 + 16 * j;
             const bool cv = pv && c < nch;
+            const int i0c = ALIGNED ? 8 * c : min(8 * c, D - 8);   // the chunk's first label
             ushort2_t s4[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
@@ -130,7 +121,10 @@ __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
                     // through a buffer resource over the whole volume
                     // (32-bit byte offsets), else a plain load
                     uint4 v;
-                    if (rsrc_ok) {
+                    if (!ALIGNED) {
+                        v = __builtin_bit_cast(uint4, __builtin_nontemporal_load(
+                                                          (const ushort8_t *)(a.in[b] + p * D + i0c)));
+                    } else if (rsrc_ok) {
                         const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
                             const_cast<uint16_t *>(a.in[b]), 0, (int)(uint32_t)vol_bytes, 0x00020000);
                         v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
@@ -149,7 +143,7 @@ __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
                 acc[j][e] = __builtin_bit_cast(uint32_t, s4[e]);
                 if (cv) {
                     const uint32_t lo = acc[j][e] & 0xFFFFu, hi = acc[j][e] >> 16;
-                    const uint32_t i0 = (uint32_t)(8 * c + 2 * e);
+                    const uint32_t i0 = (uint32_t)(i0c + 2 * e);
                     const uint32_t k0 = (lo << 16) | i0, k1 = (hi << 16) | (i0 + 1);
                     key = k0 < key ? k0 : key;
                     key = k1 < key ? k1 : key;
@@ -166,9 +160,10 @@ __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
             const int c = l16 + 16 * j;
+            const int i0c = ALIGNED || c >= nch ? 8 * c : min(8 * c, D - 8);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int i = 8 * c + e;
+                const int i = i0c + e;
                 const uint32_t v = (e & 1) ? (acc[j][e >> 1] >> 16) : (acc[j][e >> 1] & 0xFFFFu);
                 if (has_m && i == best - 1) cm = v;
                 if (has_p && i == best + 1) cp = v;
@@ -187,22 +182,6 @@ __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
 
 template <int K>
 static void launch_k(const SgmArgs &a, bool win, bool sn, dim3 grid, hipStream_t s) {
-    if (a.final_mode) {
-        const size_t N = (size_t)a.w * a.h;
-        if ((a.D & 7) == 0) {
-            unsigned blocks = (unsigned)std::min<size_t>((N + 15) / 16, 65536);
-            const int ncb = ((a.D >> 3) + 15) / 16;   // 8-label chunks per lane
-            switch (ncb) {
-                case 1: hipLaunchKernelGGL((k_wta16<1>), dim3(blocks), dim3(256), 0, s, a); return;
-                case 2: hipLaunchKernelGGL((k_wta16<2>), dim3(blocks), dim3(256), 0, s, a); return;
-                case 3: hipLaunchKernelGGL((k_wta16<3>), dim3(blocks), dim3(256), 0, s, a); return;
-                default: hipLaunchKernelGGL((k_wta16<4>), dim3(blocks), dim3(256), 0, s, a); return;
-            }
-        }
-        unsigned blocks = (unsigned)std::min<size_t>((N + 3) / 4, 65536);
-        hipLaunchKernelGGL((k_wta<K>), dim3(blocks), dim3(256), 0, s, a);
-        return;
-    }
 #define FMVS_SGM(W_, S_, P_)                                                                  \
     if (win == W_ && sn == S_ && (a.pg != 0) == P_) {                                         \
         if (a.n_fam == 1)                                                                     \
@@ -221,12 +200,28 @@ static void launch_k(const SgmArgs &a, bool win, bool sn, dim3 grid, hipStream_t
 }
 
 
-// Packed two-label kernel when every family window is even (all variants);
-// the one-label kernel otherwise.
+static void launch_wta(const SgmArgs &a, hipStream_t s) {
+    const size_t N = (size_t)a.w * a.h;
+    if (a.D < 8) {
+        hipLaunchKernelGGL(k_wta_few, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, a);
+        return;
+    }
+    const dim3 grid((unsigned)std::min<size_t>((N + 15) / 16, 65536)), block(256);
+    const bool al = (a.D & 7) == 0;
+    switch ((a.D + 127) / 128) {   // 8-label chunks per lane
+        case 1: al ? k_wta16<1, true><<<grid, block, 0, s>>>(a) : k_wta16<1, false><<<grid, block, 0, s>>>(a); return;
+        case 2: al ? k_wta16<2, true><<<grid, block, 0, s>>>(a) : k_wta16<2, false><<<grid, block, 0, s>>>(a); return;
+        case 3: al ? k_wta16<3, true><<<grid, block, 0, s>>>(a) : k_wta16<3, false><<<grid, block, 0, s>>>(a); return;
+        default: al ? k_wta16<4, true><<<grid, block, 0, s>>>(a) : k_wta16<4, false><<<grid, block, 0, s>>>(a); return;
+    }
+}
+
 __global__ void k_zero_u32(unsigned *p) {
     if (threadIdx.x == 0) *p = 0u;
 }
 
+// Packed two-label kernel when every family window is even (all variants);
+// the one-label kernel otherwise.
 static bool use_packed(const SgmArgs &a) {
     if (a.final_mode || (a.D & 1)) return false;
     for (int f = 0; f < a.n_fam; ++f)
@@ -243,7 +238,12 @@ hipError_t launch_sgm(const SgmArgs &a0, hipStream_t s) {
     for (int i = 0; i < a.n_dirs; ++i) a.path_begin[i + 1] = a.path_begin[i] + sgm_paths(a.dirs[i], a.w, a.h);
     for (int i = a.n_dirs + 1; i < 9; ++i) a.path_begin[i] = a.path_begin[a.n_dirs];
     int paths = a.path_begin[a.n_dirs];
-    if (paths == 0 && !a.final_mode) return hipSuccess;
+    if (a.final_mode) {
+        if (a.D > kMaxLabels) return hipErrorInvalidValue;
+        launch_wta(a, s);
+        return hipGetLastError();
+    }
+    if (paths == 0) return hipSuccess;
     dim3 grid((unsigned)((paths + WAVES - 1) / WAVES));
     bool win = a.offs != nullptr, sn = a.dI != nullptr;
     if (a.pg && (sn || a.sumG > kMaxPgPlanes || !a.delta)) return hipErrorInvalidValue;

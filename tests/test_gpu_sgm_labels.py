@@ -1,0 +1,51 @@
+"""Aggregation and winner-takes-all over label counts at the edges of their
+layouts (16-byte label chunks, a lane's label pairs, family borders), odd and
+even windows, against the CPU oracle (whole numbers: equal)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hd():
+    import paper_2112_00821_amd as fm
+    with fm.Handle(fm.default_config()) as h:
+        yield h
+
+
+def _winner(Sbar, W):
+    """Winner and the aggregates (before, at, after) it inside its family."""
+    best = np.argmin(Sbar, axis=-1)
+    first = np.concatenate([[0], np.cumsum(W)])
+    fam = np.searchsorted(first, best, side="right") - 1
+    at = lambda i: np.take_along_axis(Sbar, np.clip(i, 0, Sbar.shape[-1] - 1)[..., None], -1)[..., 0]
+    before = np.where(best > first[fam], at(best - 1), 0xFFFF)
+    after = np.where(best + 1 < first[fam + 1], at(best + 1), 0xFFFF)
+    return best, np.stack([before, at(best), after], -1)
+
+
+@pytest.mark.parametrize("paths,sn,W", [
+    (8, True, [1]), (4, True, [2]), (8, True, [3]), (8, False, [7]), (8, True, [8]), (8, True, [9]),
+    (8, True, [15]), (4, False, [17]), (8, True, [97]), (8, False, [127]), (8, True, [128]), (8, True, [129]),
+    (8, True, [255]), (4, True, [257]), (8, True, [511]), (8, False, [512]),
+    (8, True, [1, 1, 1]), (8, True, [2, 1, 6]), (8, False, [7, 4, 33, 2]), (8, True, [33, 32, 31, 1]),
+    (8, True, [1] * 8), (8, True, [63] * 8), (4, True, [65] * 7 + [57]),
+])
+def test_label_counts(orc, hd, paths, sn, W):
+    rng = np.random.default_rng(sum(W) * 17 + len(W))
+    h, w, D, F = 11, 14, sum(W), len(W)
+    G = [wf + 5 for wf in W]
+    S = rng.integers(0, 64, (h, w, D), dtype=np.uint8)
+    offs = np.stack([rng.integers(0, 6, (h, w)) for _ in G]).astype(np.int32)
+    dI = rng.integers(-7, 8, (8, h, w, F)).astype(np.int8) if sn else None
+    ref = rng.integers(0, 256, (h, w), dtype=np.uint8)
+    lut = orc.p2_lut(8, 1, 64, 8.0, 10.0)
+    Sbar, Lr = orc.sgm(S, W, 8, lut, ref, paths, offs=offs, dI=dI, want_lr=True)
+    r = hd.stage_sgm(hd.upload(S), W, 8, lut, hd.upload(ref), paths, offs=hd.upload(offs),
+                     dI=hd.upload(dI) if sn else None, want_lr=True, want_sbar=True)
+    best, c3 = _winner(Sbar, W)
+    assert np.array_equal(r["Lr"].numpy(), Lr)
+    assert np.array_equal(r["Sbar"].numpy(), Sbar)
+    assert np.array_equal(r["wta"].numpy(), best)
+    assert np.array_equal(r["c3"].numpy(), c3)
