@@ -304,7 +304,13 @@ __device__ __forceinline__ uint32_t as_u32(u16x2 v) { return __builtin_bit_cast(
 // (row base = pixel of the step): the lane offset is the only vector
 // operand, and lanes past the label count read 0 and drop their stores by
 // the resource's range check.  With PG the same kernel runs the
-// path-gradient variant (Eq. sgm-smooth-pg).
+// path-gradient variant (Eq. sgm-smooth-pg): its plane jump is five 64-bit
+// quotients a step, the same in every lane, so a step was bound by their
+// issue (960x540 x 128 labels, 3 levels: 1.83 ms against about 0.4 ms of the
+// recursion alone).  The reciprocals of a pixel's divisors are taken once
+// per block, a lane a step, those of the plane list once per workgroup, and
+// the quotients follow in two fused multiply-adds with the same bits:
+// 1.10 ms.
 // Wave-uniform copies of values read from an argument block (its arrays
 // indexed by a uniform index stay uniform, wherever the block lives).
 __device__ __forceinline__ int rfl(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -323,13 +329,43 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void *p, int by
 constexpr int PK_G2 = 6;
 constexpr int PK_LW = (kMaxLabels + 2 * PK_G2 * kMaxFam) / 2 + 1;   // 32-bit words per buffer, last one a sink
 
+// Path gradient: a plane's delta and its reciprocal.
+struct PgPlane {
+    double delta, recip;
+};
+
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// x / b, correctly rounded, from r = 1 / b correctly rounded: the remainder
+// of the first quotient is exact in a fused multiply-add, and the corrected
+// quotient rounds as the division does (P. Markstein, IBM J. Res. Dev. 34
+// (1990)).  Zeros, infinities and NaN as the division gives them.
+__device__ __forceinline__ double div_by(double x, double b, double r) {
+    const double q = x * r;
+    return __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-q, b, x), r, q), b, x);
+}
+
+// 1 / b, correctly rounded, from an estimate a few units in the last place
+// off: two steps of Newton's iteration, the second on a faithful value (a
+// divisor with every mantissa bit set could end one unit off).
+__device__ __forceinline__ double recip_from(double b, double r) {
+    r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+    r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+    return __builtin_amdgcn_div_fixup(r, b, 1.0);
+}
+
 // One path of the two-label kernel: path index `path` of the frame a (all
 // its directions' paths numbered by a.path_begin), run by one wavefront with
 // the P2 table s_lut and (path gradient) the plane lists pdelta in LDS, and
 // buf0 / buf1 its two LDS predecessor buffers.
 template <int KP, int NF, bool WIN, bool SN, bool PG>
 __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, const int *s_lut,
-                                            const double *pdelta, uint32_t *buf0, uint32_t *buf1) {
+                                            const PgPlane *planes, uint32_t *buf0, uint32_t *buf1) {
     constexpr int PF = KP >= 2 ? 8 : 16;   // steps per block (ring depth): fewer registers for many labels
     constexpr int G2 = PK_G2;
     constexpr int LW = PK_LW;
@@ -408,7 +444,9 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
     };
     int c_ref;
     int c_off[NF], c_di[NF];
-    auto finish_block = [&](const BlockRaw &r) {
+    // path gradient: -n^T K^-1 p of the block's pixels and its reciprocal
+    double b_c[NF], b_r[NF];
+    auto finish_block = [&](int t0, const BlockRaw &r) {
         const int d = r.i0 - r.i1;
         c_ref = r.first ? 0 : s_lut[d < 0 ? -d : d];
 #pragma unroll
@@ -416,10 +454,21 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
             c_off[f] = r.off[f];
             c_di[f] = r.di[f];
         }
+        if (PG) {
+            const int t = t0 + (lane & (PF - 1));
+            double rp[3];
+            ray_of(a.Kinv, (pg.sx + t * pg.dx) + 0.5, (pg.sy + t * pg.dy) + 0.5, rp);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const double *n = a.fam_n[f < F ? f : 0];
+                b_c[f] = -(n[0] * rp[0] + n[1] * rp[1] + n[2] * rp[2]);
+                b_r[f] = 1.0 / b_c[f];
+            }
+        }
     };
     BlockRaw raw;
     issue_block(0, raw);
-    finish_block(raw);
+    finish_block(0, raw);
 
     // ring of cost byte pairs, PF steps ahead (steps past the path's end
     // re-read its last pixel)
@@ -438,14 +487,17 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
 #pragma unroll
     for (int f = 0; f < NF; ++f) oq[f] = 0;
     // path-gradient state: depths of the last two minimum-cost points, 2/d
-    // of each, and -n^T K^-1 p of the previous pixel per family.  Values
-    // carried from one step to the next are the same doubles the formulas
-    // would recompute (the ray and its dot products of a pixel, and
-    // 1/d = (2/d) / 2, exact in binary floating point).
+    // of each, and -n^T K^-1 p of the previous pixel per family with its
+    // reciprocal.  Values carried from one step to the next are the same
+    // doubles the formulas would recompute (the ray and its dot products of a
+    // pixel, and 1/d = (2/d) / 2, exact in binary floating point).
     double dq1 = 0.0, dq2 = 0.0, a1 = 0.0, a2 = 0.0;
-    double c_prev[NF];
+    double c_prev[NF], r_prev[NF], r_step[NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) c_prev[f] = 0.0;
+    for (int f = 0; f < NF; ++f) {
+        c_prev[f] = r_prev[f] = 0.0;
+        r_step[f] = PG ? 1.0 / a.step[f < F ? f : 0] : 0.0;
+    }
 
     // Row pointers advance by one path step at a time (two scalar adds)
     // instead of being recomputed from the step index: s_ahead is the cost
@@ -486,7 +538,7 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
         for (int f = 0; f < NF; ++f) op[f] = WIN ? __builtin_amdgcn_readlane(c_off[f], u) : 0;
         uint32_t *cur = (u & 1) ? buf1 : buf0;
         const uint32_t *prev = (u & 1) ? buf0 : buf1;
-        double c_cur[NF];   // path gradient: -n^T K^-1 p of this step's pixel
+        double c_cur[NF], r_cur[NF];   // path gradient: -n^T K^-1 p of this step's pixel and its reciprocal
         {
             // splats of uniform 16-bit values (the packed instructions take
             // them as one scalar operand)
@@ -502,15 +554,11 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
                 if (SN) v += __builtin_amdgcn_readlane(c_di[f], u);
                 sh[f] = v;
             }
-            // -n^T K^-1 p of this step's pixel per family (path gradient)
             if (PG) {
-                const int px = pg.sx + t * pg.dx, py = pg.sy + t * pg.dy;
-                double rp[3];
-                ray_of(a.Kinv, px + 0.5, py + 0.5, rp);
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
-                    const double *n = a.fam_n[f < F ? f : 0];
-                    c_cur[f] = -(n[0] * rp[0] + n[1] * rp[1] + n[2] * rp[2]);
+                    c_cur[f] = lane_f64(b_c[f], u);
+                    r_cur[f] = lane_f64(b_r[f], u);
                 }
             }
             if (PG && t >= 2 && dq1 > 0.0 && dq2 > 0.0) {
@@ -523,11 +571,12 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
                     if (f >= F) break;
                     const double cp = c_cur[f], cq = c_prev[f];
                     if (!(cp > 0.0) || !(cq > 0.0)) continue;
-                    const double ip = inv / cp;
-                    const double iq = 1.0 / (dq1 * cq);
-                    double v = (ip - iq) / a.step[f];
+                    const double ip = div_by(inv, cp, r_cur[f]);
+                    const double iq = recip_from(dq1 * cq, 0.5 * a1 * r_prev[f]);
+                    double v = div_by(ip - iq, a.step[f], r_step[f]);
                     v = fmin(fmax(v, -7.0), 7.0);
-                    sh[f] += (int)round(v);
+                    // round half away from zero
+                    sh[f] += (int)(v + __builtin_copysign(0x1.fffffffffffffp-2, v));
                 }
             }
 #pragma unroll
@@ -593,17 +642,24 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
             int f = 0;
             while (f + 1 < F && bi >= a.foff[f + 1]) ++f;
             const int g = (WIN ? op[f] : 0) + (bi - a.foff[f]);
-            double cf = c_cur[0];
+            double cf = c_cur[0], rf = r_cur[0];
 #pragma unroll
-            for (int ff = 1; ff < NF; ++ff)
-                if (ff == f) cf = c_cur[ff];
-            const double den = -cf;   // n^T K^-1 p, exactly
+            for (int ff = 1; ff < NF; ++ff) {
+                if (ff == f) {
+                    cf = c_cur[ff];
+                    rf = r_cur[ff];
+                }
+            }
+            const PgPlane pl = planes[a.goff[f] + g];
             dq2 = dq1;
             a2 = a1;
-            dq1 = den < 0.0 ? -pdelta[a.goff[f] + g] / den : 0.0;
-            a1 = dq1 > 0.0 ? 2.0 / dq1 : 0.0;
+            dq1 = cf > 0.0 ? div_by(pl.delta, cf, rf) : 0.0;
+            a1 = dq1 > 0.0 ? 2.0 * recip_from(dq1, cf * pl.recip) : 0.0;
 #pragma unroll
-            for (int ff = 0; ff < NF; ++ff) c_prev[ff] = c_cur[ff];
+            for (int ff = 0; ff < NF; ++ff) {
+                c_prev[ff] = c_cur[ff];
+                r_prev[ff] = r_cur[ff];
+            }
         } else {
             const uint32_t mw = as_u32(m2);
             const uint32_t lo = mw & 0xFFFFu, hi = mw >> 16;
@@ -622,13 +678,13 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
         issue_block(t0 + PF, raw);
 #pragma unroll
         for (int u = 0; u < PF; ++u) step(t0 + u, u, false);
-        finish_block(raw);
+        finish_block(t0 + PF, raw);
     }
     for (; t0 + PF <= len; t0 += PF) {
         issue_block(t0 + PF, raw);
 #pragma unroll
         for (int u = 0; u < PF; ++u) step(t0 + u, u, true);
-        finish_block(raw);
+        finish_block(t0 + PF, raw);
     }
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
@@ -641,15 +697,15 @@ template <int KP, int NF, bool WIN, bool SN, bool PG>
 __global__ __launch_bounds__(64 * WAVES) void k_sgm_pk(const SgmArgs a) {
     __shared__ uint32_t lbuf[WAVES][2][PK_LW];
     __shared__ int s_lut[256];   // P2 by intensity change
-    __shared__ double pdelta[PG ? kMaxPgPlanes : 1];   // path gradient: the level's plane lists
+    extern __shared__ PgPlane planes[];   // path gradient: the level's plane lists (a.sumG entries)
     for (int i = threadIdx.x; i < 256; i += 64 * WAVES) s_lut[i] = a.lut[i];
     if (PG)
-        for (int i = threadIdx.x; i < a.sumG; i += 64 * WAVES) pdelta[i] = a.delta[i];
+        for (int i = threadIdx.x; i < a.sumG; i += 64 * WAVES) planes[i] = PgPlane{a.delta[i], 1.0 / a.delta[i]};
     __syncthreads();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int path = blockIdx.x * WAVES + wid;
     if (path >= a.path_begin[a.n_dirs]) return;
-    sgm_pk_path<KP, NF, WIN, SN, PG>(a, path, s_lut, pdelta, lbuf[wid][0], lbuf[wid][1]);
+    sgm_pk_path<KP, NF, WIN, SN, PG>(a, path, s_lut, planes, lbuf[wid][0], lbuf[wid][1]);
 }
 
 // The fields the aggregation reads of a frame's arguments in device memory,
@@ -715,14 +771,15 @@ __global__ __launch_bounds__(64 * WAVES) void k_sgm_pk_jobs(const SgmArgs *__res
 // at run time).  Instantiated once per KP in k_sgm_inst.hip.
 template <int KP>
 void sgm_launch_pk(const SgmArgs &a, bool win, bool sn, dim3 grid, hipStream_t s) {
+    const size_t lds = a.pg ? (size_t)a.sumG * sizeof(PgPlane) : 0;
 #define FMVS_SGMPK(W_, S_, P_)                                                                     \
     if (win == W_ && sn == S_ && (a.pg != 0) == P_) {                                              \
         if (a.n_fam == 1)                                                                          \
-            hipLaunchKernelGGL((k_sgm_pk<KP, 1, W_, S_, P_>), grid, dim3(64 * WAVES), 0, s, a);    \
+            hipLaunchKernelGGL((k_sgm_pk<KP, 1, W_, S_, P_>), grid, dim3(64 * WAVES), lds, s, a);    \
         else if (a.n_fam <= 4)                                                                     \
-            hipLaunchKernelGGL((k_sgm_pk<KP, 4, W_, S_, P_>), grid, dim3(64 * WAVES), 0, s, a);    \
+            hipLaunchKernelGGL((k_sgm_pk<KP, 4, W_, S_, P_>), grid, dim3(64 * WAVES), lds, s, a);    \
         else                                                                                       \
-            hipLaunchKernelGGL((k_sgm_pk<KP, kMaxFam, W_, S_, P_>), grid, dim3(64 * WAVES), 0, s, a); \
+            hipLaunchKernelGGL((k_sgm_pk<KP, kMaxFam, W_, S_, P_>), grid, dim3(64 * WAVES), lds, s, a); \
         return;                                                                                    \
     }
     FMVS_SGMPK(false, false, false)

@@ -49,3 +49,28 @@ def test_label_counts(orc, hd, paths, sn, W):
     assert np.array_equal(r["Sbar"].numpy(), Sbar)
     assert np.array_equal(r["wta"].numpy(), best)
     assert np.array_equal(r["c3"].numpy(), c3)
+
+
+@pytest.mark.parametrize("w,h,W,G,tilt", [
+    (33, 17, [16], [16], 0.0), (40, 31, [24, 8], [40, 9], 0.6), (17, 50, [130], [200], 0.3),
+    (35, 20, [2, 4, 6, 8, 10], [2, 7, 6, 30, 11], 1.5),      # some pixels see a plane from behind
+    (21, 33, [7, 12], [9, 12], 0.6),                         # an odd window
+])
+def test_path_gradient_planes(orc, hd, w, h, W, G, tilt):
+    rng = np.random.default_rng(w * h + sum(G))
+    F, D = len(W), sum(W)
+    Kinv = np.linalg.inv(np.array([[0.8 * w, 0, w / 2], [0, 0.8 * w, h / 2], [0, 0, 1.0]]))
+    fam_n = np.array([[rng.uniform(-tilt, tilt), rng.uniform(-tilt, tilt), -1.0] for _ in W])
+    near, far = 2.0, 40.0
+    fam_delta = np.concatenate([1.0 / np.linspace(1.0 / near, 1.0 / far, g) for g in G])
+    step = np.array([(1.0 / near - 1.0 / far) / (g - 1) for g in G])
+    S = rng.integers(0, 64, (h, w, D), dtype=np.uint8)
+    offs = np.stack([rng.integers(0, g - wf + 1, (h, w)) for g, wf in zip(G, W)]).astype(np.int32)
+    ref = rng.integers(0, 256, (h, w), dtype=np.uint8)
+    lut = orc.p2_lut(8, 1, 64, 8.0, 10.0)
+    geom = dict(G=G, fam_delta=fam_delta, fam_n=fam_n, Kinv=Kinv, step=step)
+    Sbar, Lr = orc.sgm(S, W, 8, lut, ref, 8, offs=offs, want_lr=True, pg=geom)
+    r = hd.stage_sgm_pg(hd.upload(S), W, G, 8, lut, hd.upload(ref), 8, fam_delta, fam_n, Kinv, step,
+                        offs=hd.upload(offs), want_lr=True, want_sbar=True)
+    assert np.array_equal(r["Lr"].numpy(), Lr)
+    assert np.array_equal(r["Sbar"].numpy(), Sbar)
