@@ -90,10 +90,68 @@ typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 // label count is no multiple of 8 the last chunk starts 8 before the end, so
 // that every load stays inside its pixel: the labels it repeats have the same
 // sums.  Rows then start at 2-byte steps and loads are not aligned: 641x479 x
-// 97 labels 0.26 ms with one label a lane, 0.10 ms so.
+// 97 labels 0.26 ms with one label a lane, 0.095 ms so.  The narrow forms read
+// 9 bits a label (narrow_sums).
 typedef unsigned short ushort8_t __attribute__((ext_vector_type(8), aligned(2)));
-template <int NCH, bool ALIGNED>
+typedef uint32_t uint2_t __attribute__((ext_vector_type(2)));
+
+// Aggregates of 8 labels (chunk c) of pixel p from NB directions' narrow path
+// costs: NB costs S plus the heights, a byte each, plus 256 for each 9th bit.
+// The bits of 8 labels are a nibble of the even labels' word and one of the
+// odd labels'; a product spreads a nibble over four byte counters.
+template <int NB, int NCH>
+__device__ __forceinline__ void narrow_sums(const SgmArgs &a, size_t p, int c, int j, ushort2_t (&s4)[4]) {
+    const size_t N = (size_t)a.w * a.h;
+    const int D = a.D;
+    const size_t bits = narrow_bits_at(N, D) + (p * NCH + j) * 16 + (size_t)((c & 8) ? 8 : 0);
+    const int at = 4 * (c & 7);
+    const uint2_t s = *(const uint2_t *)(a.S + p * D + 8 * c);
+    uint2_t v[NB], m[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const uint8_t *in = (const uint8_t *)a.in[b];
+        v[b] = __builtin_nontemporal_load((const uint2_t *)(in + p * D + 8 * c));
+        m[b] = *(const uint2_t *)(in + bits);
+    }
+    constexpr uint32_t kLow = 0x00FF00FFu;
+    uint32_t t[2][2], cnt[2] = {0, 0};   // [word][odd label], the counters [odd label]
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        t[i][0] = (s[i] & kLow) * NB;
+        t[i][1] = ((s[i] >> 8) & kLow) * NB;
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            t[i][0] += v[b][i] & kLow;
+            t[i][1] += (v[b][i] >> 8) & kLow;
+            cnt[i] += __umul24(__builtin_amdgcn_ubfe(m[b][i], at, 4), 0x204081u) & 0x01010101u;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t up = i ? 0x030c020cu : 0x010c000cu;
+        const uint32_t e = t[i][0] + __builtin_amdgcn_perm(0u, cnt[0], up);
+        const uint32_t o = t[i][1] + __builtin_amdgcn_perm(0u, cnt[1], up);
+        s4[2 * i] = __builtin_bit_cast(ushort2_t, __builtin_amdgcn_perm(o, e, 0x05040100u));
+        s4[2 * i + 1] = __builtin_bit_cast(ushort2_t, __builtin_amdgcn_perm(o, e, 0x07060302u));
+    }
+    // the next chunk's loads stay behind this one's sums: the registers of
+    // several chunks would leave two wavefronts a SIMD
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t t4 = __builtin_bit_cast(uint32_t, s4[i]);
+        asm volatile("" : "+v"(t4) : : "memory");
+        s4[i] = __builtin_bit_cast(ushort2_t, t4);
+    }
+}
+
+enum WtaForm { kWtaAligned, kWtaUnaligned, kWtaNarrow4, kWtaNarrow8 };
+template <int NCH, int FORM>
 __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
+    constexpr bool ALIGNED = FORM != kWtaUnaligned;
+    constexpr int NARROW = FORM == kWtaNarrow4 ? 4 : FORM == kWtaNarrow8 ? 8 : 0;   // directions
     const int lane = threadIdx.x & 63;
     const int row = lane >> 4, l16 = lane & 15;
     const size_t N = (size_t)a.w * a.h;
@@ -114,9 +172,10 @@ __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
             const bool cv = pv && c < nch;
             const int i0c = ALIGNED ? 8 * c : min(8 * c, D - 8);   // the chunk's first label
             ushort2_t s4[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+            if constexpr (NARROW != 0) narrow_sums<NARROW, NCH>(a, pv ? p : N - 1, min(c, nch - 1), j, s4);
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                if (b < a.n_in && cv) {
+                if (!NARROW && b < a.n_in && cv) {
                     // each path cost is read once: non-temporal load
                     // through a buffer resource over the whole volume
                     // (32-bit byte offsets), else a plain load
@@ -207,13 +266,43 @@ static void launch_wta(const SgmArgs &a, hipStream_t s) {
         return;
     }
     const dim3 grid((unsigned)std::min<size_t>((N + 15) / 16, 65536)), block(256);
-    const bool al = (a.D & 7) == 0;
-    switch ((a.D + 127) / 128) {   // 8-label chunks per lane
-        case 1: al ? k_wta16<1, true><<<grid, block, 0, s>>>(a) : k_wta16<1, false><<<grid, block, 0, s>>>(a); return;
-        case 2: al ? k_wta16<2, true><<<grid, block, 0, s>>>(a) : k_wta16<2, false><<<grid, block, 0, s>>>(a); return;
-        case 3: al ? k_wta16<3, true><<<grid, block, 0, s>>>(a) : k_wta16<3, false><<<grid, block, 0, s>>>(a); return;
-        default: al ? k_wta16<4, true><<<grid, block, 0, s>>>(a) : k_wta16<4, false><<<grid, block, 0, s>>>(a); return;
+    const int form = a.narrow ? (a.n_in == 4 ? kWtaNarrow4 : kWtaNarrow8) : (a.D & 7) ? kWtaUnaligned : kWtaAligned;
+#define FMVS_WTA(N_)                                                                              \
+    switch (form) {                                                                              \
+        case kWtaAligned: k_wta16<N_, kWtaAligned><<<grid, block, 0, s>>>(a); return;            \
+        case kWtaUnaligned: k_wta16<N_, kWtaUnaligned><<<grid, block, 0, s>>>(a); return;        \
+        case kWtaNarrow4: k_wta16<N_, kWtaNarrow4><<<grid, block, 0, s>>>(a); return;            \
+        default: k_wta16<N_, kWtaNarrow8><<<grid, block, 0, s>>>(a); return;                     \
     }
+    switch ((a.D + 127) / 128) {   // 8-label chunks per lane
+        case 1: FMVS_WTA(1)
+        case 2: FMVS_WTA(2)
+        case 3: FMVS_WTA(3)
+        default: FMVS_WTA(4)
+    }
+#undef FMVS_WTA
+}
+
+// One thread per label pair.
+__global__ __launch_bounds__(256) void k_widen(const uint8_t *__restrict__ S, const uint8_t *__restrict__ in, size_t N,
+                                               int D, uint16_t *__restrict__ dst) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t p = i / (unsigned)(D / 2);
+    if (p >= N) return;
+    const int pair = (int)(i - p * (unsigned)(D / 2));
+    const uint32_t *m = (const uint32_t *)(in + narrow_bits_at(N, D)) +
+                        (p * ((D + 127) / 128) + (pair >> 6)) * 4 + 2 * ((pair >> 5) & 1);
+    for (int o = 0; o < 2; ++o) {
+        const size_t at = p * D + 2 * pair + o;
+        dst[at] = (uint16_t)(S[at] + in[at] + (((m[o] >> (pair & 31)) & 1u) << 8));
+    }
+}
+
+hipError_t launch_widen(const uint8_t *S, const void *narrow, int w, int h, int D, uint16_t *dst, hipStream_t s) {
+    const size_t N = (size_t)w * h, n = N * (D / 2);
+    hipLaunchKernelGGL(k_widen, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, S, (const uint8_t *)narrow, N, D,
+                       dst);
+    return hipGetLastError();
 }
 
 __global__ void k_zero_u32(unsigned *p) {
@@ -232,6 +321,24 @@ static bool use_packed(const SgmArgs &a) {
     return !(e && std::atoi(e) != 0);
 }
 
+// The path costs of a direction are S plus a height of at most P2, so where
+// no P2 exceeds 511 they can be held as a byte a label and a 9th bit.  The
+// two-label kernel then writes 9 bits a label and direction and the winner's
+// pass reads them, in place of 16 each; both are bound by those bytes on
+// large frames (1920x1080 x 128 labels, 3 levels, 8 paths: 1.87 -> 1.60 ms
+// and 0.88 -> 0.71 ms; 2704x1520, 4 families: 11.0 -> 9.7 and 5.7 -> 4.6 ms).
+// Below 2^27 labels the packing costs what the bytes save (1280x720 x 128,
+// 4 paths: 0.36 -> 0.39 and 0.18 -> 0.14 ms; 640x480 x 168: 0.48 -> 0.52 and
+// 0.27 -> 0.24 ms), as it does with the path gradient's arithmetic beside it
+// (1.03 -> 1.06 ms).  The winner's pass takes whole chunks of 8 labels, and
+// from 16 labels on the bits (a word of 16 bytes per 128 labels) fit behind
+// the bytes in the room of the 16-bit form.
+bool sgm_narrow(const SgmArgs &a) {
+    if ((a.D & 7) || a.D < 16 || a.D > kMaxLabels || a.n_fam > 4 || a.pg || !use_packed(a)) return false;
+    if ((size_t)a.w * a.h * a.D < (size_t)1 << 27) return false;
+    return *std::max_element(a.lut, a.lut + 256) <= 511 && *std::min_element(a.lut, a.lut + 256) >= 0;
+}
+
 hipError_t launch_sgm(const SgmArgs &a0, hipStream_t s) {
     SgmArgs a = a0;
     a.path_begin[0] = 0;
@@ -247,7 +354,7 @@ hipError_t launch_sgm(const SgmArgs &a0, hipStream_t s) {
     dim3 grid((unsigned)((paths + WAVES - 1) / WAVES));
     bool win = a.offs != nullptr, sn = a.dI != nullptr;
     if (a.pg && (sn || a.sumG > kMaxPgPlanes || !a.delta)) return hipErrorInvalidValue;
-    if (use_packed(a)) {
+    if (a.narrow || use_packed(a)) {
         switch ((a.D + 127) / 128) {
             case 1: sgm_launch_pk<1>(a, win, sn, grid, s); break;
             case 2: sgm_launch_pk<2>(a, win, sn, grid, s); break;

@@ -311,6 +311,12 @@ __device__ __forceinline__ uint32_t as_u32(u16x2 v) { return __builtin_bit_cast(
 // per block, a lane a step, those of the plane list once per workgroup, and
 // the quotients follow in two fused multiply-adds with the same bits:
 // 1.10 ms.
+// With NARROW the path costs leave as 9-bit heights above S (sgm_narrow): a
+// byte a label at once, the 9th bits gathered by two ballots a step in lane
+// 4u .. 4u + 3 of step u of the block (even and odd labels of pairs 0-31, then
+// of pairs 32-63) and stored once per block.  The kernel is bound by its bytes
+// on large frames (1920x1080 x 128 labels, level 0: 7.26 GB in 1.58 ms, 4.6 of
+// the 4.9 TB/s a copy reaches).
 // Wave-uniform copies of values read from an argument block (its arrays
 // indexed by a uniform index stay uniform, wherever the block lives).
 __device__ __forceinline__ int rfl(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -359,13 +365,61 @@ __device__ __forceinline__ double recip_from(double b, double r) {
     return __builtin_amdgcn_div_fixup(r, b, 1.0);
 }
 
+// A shift's three aligned words of taps: their byte step from the words of
+// no shift, and the byte selector of the first tap pair (the others follow).
+// The four 16-bit entries q .. q + 3 start at q = j - 1, j even for a shift
+// of 0.
+struct Taps {
+    int step;
+    uint32_t sel;
+};
+__device__ __forceinline__ Taps taps_of(int shift) {
+    return Taps{4 * ((shift - 1) >> 1), 0x03020100u + (uint32_t)(~shift & 1) * 0x02020202u};
+}
+typedef __attribute__((address_space(3))) uint32_t LdsWord;
+
+// (the compiler's own operation; it has no builtin)
+__device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");
+
+// Where the 9th bits start in a direction's narrow path costs of N pixels.
+__host__ __device__ inline size_t narrow_bits_at(size_t N, int D) { return (N * D + 15) & ~(size_t)15; }
+
+// One wavefront's LDS: two predecessor buffers (the last step's path costs,
+// this step's) and a block's shifts by family (path gradient: their plain
+// values in .step).
+struct PkLds {
+    uint32_t cost[2][PK_LW];
+    Taps shift[16][kMaxFam];
+};
+
+// Smaller 16-bit half of a word.  A lane-crossing read of the result needs
+// two wait states; they are in the block unless another instruction comes
+// first (OTHER).
+template <bool OTHER>
+__device__ __forceinline__ uint32_t min_of_halves(uint32_t v) {
+    uint32_t r;
+    if (OTHER)
+        asm("v_min_u32_sdwa %0, %1, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1"
+            : "=v"(r) : "v"(v));
+    else
+        asm("v_min_u32_sdwa %0, %1, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1\n\ts_nop 1"
+            : "=v"(r) : "v"(v));
+    return r;
+}
+
+__device__ __forceinline__ int med3_i32(int v, int lo, int hi) {
+    int r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "v"(lo), "v"(hi));
+    return r;
+}
+
 // One path of the two-label kernel: path index `path` of the frame a (all
 // its directions' paths numbered by a.path_begin), run by one wavefront with
-// the P2 table s_lut and (path gradient) the plane lists pdelta in LDS, and
-// buf0 / buf1 its two LDS predecessor buffers.
-template <int KP, int NF, bool WIN, bool SN, bool PG>
+// the P2 table s_lut and (path gradient) the plane lists in LDS, and its own
+// LDS buffers.
+template <int KP, int NF, bool WIN, bool SN, bool PG, bool NARROW>
 __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, const int *s_lut,
-                                            const PgPlane *planes, uint32_t *buf0, uint32_t *buf1) {
+                                            const PgPlane *planes, PkLds &lds) {
     constexpr int PF = KP >= 2 ? 8 : 16;   // steps per block (ring depth): fewer registers for many labels
     constexpr int G2 = PK_G2;
     constexpr int LW = PK_LW;
@@ -386,9 +440,13 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
     const long pstride = (long)pg.dy * aw + pg.dx;
     const long p0 = (long)pg.sy * aw + pg.sx;
     const int len = pg.len;
-    const bool all_valid = D == 128 * KP;
 
-    int fam[KP], li[KP], jmax[KP], seg[KP], widx[KP];
+    int fam[KP], widx[KP];
+    // LDS byte addresses in the first predecessor buffer: of the pair's own
+    // word, and the range of its taps' first word (beyond it they are guards
+    // only)
+    const int cost0 = (int)(uint32_t)(uintptr_t)(LdsWord *)lds.cost[0];
+    int at0[KP], at_lo[KP], at_hi[KP];
     uint32_t lo8[KP];   // byte offset of the pair inside a pixel's cost row
     bool lv[KP];
 #pragma unroll
@@ -399,34 +457,45 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
         int f = 0;
         while (f + 1 < F && i >= a.foff[f + 1]) ++f;
         fam[k] = f;
-        li[k] = i - a.foff[f];
-        jmax[k] = a.W[f] + 2;
+        const int li = i - a.foff[f];
         int sb = G2;
         for (int ff = 0; ff < f; ++ff) sb += a.W[ff] + 2 * G2;
-        seg[k] = sb;
-        widx[k] = lv[k] ? (sb + li[k]) >> 1 : LW - 1;
+        at0[k] = cost0 + 2 * (sb + li);
+        at_lo[k] = cost0 + 2 * (sb - G2);
+        at_hi[k] = cost0 + 2 * (sb + a.W[f]);
+        widx[k] = lv[k] ? (sb + li) >> 1 : LW - 1;
     }
     for (int i = lane; i < LW; i += 64) {
-        buf0[i] = 0xFFFFFFFFu;
-        buf1[i] = 0xFFFFFFFFu;
+        lds.cost[0][i] = 0xFFFFFFFFu;
+        lds.cost[1][i] = 0xFFFFFFFFu;
     }
     __builtin_amdgcn_wave_barrier();
 
     const uint8_t *__restrict__ S = rflp(a.S);
-    uint16_t *__restrict__ out = rflp(a.out[slot]);
+    // path costs: 2 bytes a label, or (NARROW) a byte each and the pairs' 9th
+    // bits behind them
+    constexpr int kOut = NARROW ? 1 : 2;
+    uint8_t *__restrict__ out = (uint8_t *)rflp(a.out[slot]);
+    uint32_t *__restrict__ bits = (uint32_t *)(out + narrow_bits_at(N, D));
+    uint32_t high[KP];   // a block's 9th bits: four words a step, a word a lane
+#pragma unroll
+    for (int k = 0; k < KP; ++k) high[k] = 0;
 
     // Uniform per-step values of one block of PF steps, one vector load per
     // quantity (lane j holds step t0 + j, j < PF): the penalty P2 of the
-    // intensity change from the previous pixel, the window offsets and the
-    // surface-normal offsets.  The loads of a block are issued one block
-    // ahead and finished (the P2 lookup in LDS) when the block starts, so no
-    // load is waited for before its use.  The first step of the path gets
-    // P2 = 0: with the predecessor minimum at 0 the recursion then reduces
-    // to L = S there, so the first step needs no code of its own.
+    // intensity change from the previous pixel and the families' shifts (the
+    // step of the window offset and the surface-normal offset).  The loads of
+    // a block are issued one block ahead and finished (the P2 lookup in LDS)
+    // when the block starts, so no load is waited for before its use.  One
+    // family: P2 and the shift leave their lane in one word; several: each
+    // lane reads its family's shift of the step from LDS.  The first step of
+    // the path gets P2 = 0: with the predecessor minimum at 0 the recursion
+    // then reduces to L = S there, so the first step needs no code of its
+    // own.
     struct BlockRaw {
         int i0, i1;   // intensities at the step and at its predecessor
         bool first;
-        int off[NF], di[NF];
+        int off[NF], offp[NF], di[NF];
     };
     auto issue_block = [&](int t0, BlockRaw &r) {
         const int tl = t0 + (lane & (PF - 1));
@@ -439,20 +508,27 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             r.off[f] = (WIN && f < F) ? aoffs[(size_t)f * N + p] : 0;
+            r.offp[f] = (WIN && f < F) ? aoffs[(size_t)f * N + pp] : 0;
             r.di[f] = (SN && f < F) ? (int)adI[((size_t)dir * N + p) * F + f] : 0;
         }
     };
-    int c_ref;
-    int c_off[NF], c_di[NF];
+    int c_ref;       // P2 in the low half, one family's shift in the high half
+    int c_off[NF];   // path gradient: the window offsets
     // path gradient: -n^T K^-1 p of the block's pixels and its reciprocal
     double b_c[NF], b_r[NF];
     auto finish_block = [&](int t0, const BlockRaw &r) {
         const int d = r.i0 - r.i1;
-        c_ref = r.first ? 0 : s_lut[d < 0 ? -d : d];
+        const int p2 = r.first ? 0 : s_lut[d < 0 ? -d : d];
+        c_ref = p2;
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             c_off[f] = r.off[f];
-            c_di[f] = r.di[f];
+            // (no window is as wide as the bound)
+            const int sh = min(max(r.off[f] - r.offp[f] + r.di[f], -2 * kMaxLabels), 2 * kMaxLabels);
+            if (NF == 1)
+                c_ref = (int)__builtin_amdgcn_perm((uint32_t)sh, (uint32_t)p2, 0x05040100u);
+            else
+                lds.shift[lane & (PF - 1)][f] = PG ? Taps{sh, 0u} : taps_of(sh);
         }
         if (PG) {
             const int t = t0 + (lane & (PF - 1));
@@ -483,9 +559,6 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
 
     u16x2 L[KP];
     uint32_t Mq = 0;
-    int oq[NF];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) oq[f] = 0;
     // path-gradient state: depths of the last two minimum-cost points, 2/d
     // of each, and -n^T K^-1 p of the previous pixel per family with its
     // reciprocal.  Values carried from one step to the next are the same
@@ -505,13 +578,13 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
     // pixel), o_cur the output row of the current step.
     const long sstride = pstride * D;
     const uint8_t *s_ahead = S + (size_t)(p0 + (long)(PF < len ? PF : len - 1) * pstride) * D;
-    uint16_t *o_cur = out + (size_t)p0 * D;
+    uint8_t *o_cur = out + (size_t)p0 * D * kOut;
 
     // one step of the recursion at path position t (ring slot and block
     // lane u); clamp: the ring row may reach the path's last pixel in this
     // step (else it advances unconditionally)
     auto step = [&](const int t, const int u, const bool clamp) __attribute__((always_inline)) {
-        u16x2 sv[KP];
+        u16x2 sv[KP], dl[KP];   // costs, and the path costs above them (at most P2)
 #pragma unroll
         for (int k = 0; k < KP; ++k) sv[k] = as_u16x2(__builtin_amdgcn_perm(0u, ring[u][k], 0x0c010c00u));
         {
@@ -532,12 +605,9 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
             // precomputed address per unrolled step in scalar registers)
             asm volatile("" : "+s"(s_ahead));
         }
-        const uint32_t P2 = (uint32_t)__builtin_amdgcn_readlane(c_ref, u);
-        int op[NF];
-#pragma unroll
-        for (int f = 0; f < NF; ++f) op[f] = WIN ? __builtin_amdgcn_readlane(c_off[f], u) : 0;
-        uint32_t *cur = (u & 1) ? buf1 : buf0;
-        const uint32_t *prev = (u & 1) ? buf0 : buf1;
+        const int word = __builtin_amdgcn_readlane(c_ref, u);
+        const uint32_t P2 = (uint32_t)word & 0xFFFFu;
+        uint32_t *cur = lds.cost[u & 1];
         double c_cur[NF], r_cur[NF];   // path gradient: -n^T K^-1 p of this step's pixel and its reciprocal
         {
             // splats of uniform 16-bit values (the packed instructions take
@@ -547,13 +617,9 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
             const u16x2 mqv = (u16x2)(uint16_t)Mq;
             const uint16_t fl = (uint16_t)(Mq + P2);
             const u16x2 flv = (u16x2)fl;
-            int sh[NF];
+            int jump[NF];   // path gradient: the planes' jump
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                int v = WIN ? op[f] - oq[f] : 0;
-                if (SN) v += __builtin_amdgcn_readlane(c_di[f], u);
-                sh[f] = v;
-            }
+            for (int f = 0; f < NF; ++f) jump[f] = 0;
             if (PG) {
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
@@ -576,52 +642,65 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
                     double v = div_by(ip - iq, a.step[f], r_step[f]);
                     v = fmin(fmax(v, -7.0), 7.0);
                     // round half away from zero
-                    sh[f] += (int)(v + __builtin_copysign(0x1.fffffffffffffp-2, v));
+                    jump[f] = (int)(v + __builtin_copysign(0x1.fffffffffffffp-2, v));
                 }
             }
 #pragma unroll
             for (int k = 0; k < KP; ++k) {
-                int sft = sh[0];
+                Taps tp;
+                if (NF == 1) {
+                    tp = taps_of((word >> 16) + (PG ? jump[0] : 0));
+                } else {
+                    tp = lds.shift[u][fam[k]];
+                    if (PG) {
+                        int jf = jump[0];
 #pragma unroll
-                for (int f = 1; f < NF; ++f)
-                    if (fam[k] == f) sft = sh[f];
-                const int jm = NF == 1 ? a.W[0] + 2 : jmax[k];
-                const int sg = NF == 1 ? G2 : seg[k];
-                const int j = min(max(li[k] + sft, -4), jm);
-                const int base = sg + j;
-                // The taps (j-1, j), (j, j+1), (j+1, j+2) of the pair are the
-                // 16-bit entries q .. q+3, q = base - 1, of three aligned
-                // words A, B, C; byte permutes pick them whatever the
-                // parity of q.  One family: every lane shares that parity
-                // (the shift's); where j is clamped the words hold guards
-                // only, so the choice does not matter there.
-                const int q = base - 1;
-                const uint32_t qodd = NF == 1 ? (uint32_t)((sft & 1) ^ 1) : (uint32_t)(q & 1);
-                const uint32_t s1 = 0x03020100u + qodd * 0x02020202u;
-                const uint32_t s2 = s1 + 0x02020202u;
-                const int e0 = q >> 1;
-                const uint32_t A = prev[e0], B = prev[e0 + 1], C = prev[e0 + 2];
-                const uint32_t wm = __builtin_amdgcn_perm(B, A, s1);
-                const uint32_t w0 = __builtin_amdgcn_perm(B, A, s2);
-                const uint32_t wp = __builtin_amdgcn_perm(C, B, s1);
+                        for (int f = 1; f < NF; ++f)
+                            if (fam[k] == f) jf = jump[f];
+                        tp = taps_of(tp.step + jf);
+                    }
+                }
+                // The taps (j-1, j), (j, j+1), (j+1, j+2) of the pair come from
+                // three aligned words; byte permutes pick them whatever the
+                // parity of the shift.  (One read of 8 bytes at a 2-byte step
+                // takes the LDS longer: 1.88 -> 2.62 ms at 1920x1080 x 128.)
+                const int at = med3_i32(at0[k] + tp.step, at_lo[k], at_hi[k]);
+                const LdsWord *q = (const LdsWord *)(uintptr_t)(uint32_t)(at + (u & 1 ? 0 : (int)sizeof lds.cost[0]));
+                const uint32_t A = q[0], B = q[1], C = q[2];
+                const uint32_t wm = __builtin_amdgcn_perm(B, A, tp.sel);
+                const uint32_t w0 = __builtin_amdgcn_perm(B, A, tp.sel + 0x02020202u);
+                const uint32_t wp = __builtin_amdgcn_perm(C, B, tp.sel);
                 const u16x2 cm = as_u16x2(wm), c0 = as_u16x2(w0), cp = as_u16x2(wp);
                 const u16x2 c1 = __builtin_elementwise_add_sat(__builtin_elementwise_min(cm, cp), p1v);
                 u16x2 best = __builtin_elementwise_min(c0, c1);
                 best = __builtin_elementwise_min(best, flv);
-                L[k] = sv[k] + (best - mqv);
+                dl[k] = best - mqv;
+                L[k] = sv[k] + dl[k];
             }
         }
         u16x2 m2 = as_u16x2(0xFFFFFFFFu);
-        const __amdgpu_buffer_rsrc_t ro = row_rsrc(o_cur, 2 * D);
-        o_cur += sstride;
+        const __amdgpu_buffer_rsrc_t ro = row_rsrc(o_cur, kOut * D);
+        o_cur += kOut * sstride;
         asm volatile("" : "+s"(o_cur));
 #pragma unroll
         for (int k = 0; k < KP; ++k) {
             cur[widx[k]] = as_u32(L[k]);
             // non-temporal: the path costs are read once, by the
             // winner-takes-all pass, long after the caches have turned over
-            __builtin_amdgcn_raw_buffer_store_b32(as_u32(L[k]), ro, 2 * lo8[k], 0, kNonTemporal);
-            m2 = __builtin_elementwise_min(m2, (all_valid || lv[k]) ? L[k] : as_u16x2(0xFFFFFFFFu));
+            if (NARROW) {
+                const uint32_t d = as_u32(dl[k]);
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)__builtin_amdgcn_perm(0u, d, 0x0c0c0200u), ro, lo8[k], 0,
+                                                      kNonTemporal);
+                const uint64_t even = __builtin_amdgcn_ballot_w64((uint16_t)d > 255);
+                const uint64_t odd = __builtin_amdgcn_ballot_w64((uint16_t)(d >> 16) > 255);
+                high[k] = write_lane((uint32_t)even, 4u * u, high[k]);
+                high[k] = write_lane((uint32_t)odd, 4 * u + 1, high[k]);
+                high[k] = write_lane((uint32_t)(even >> 32), 4 * u + 2, high[k]);
+                high[k] = write_lane((uint32_t)(odd >> 32), 4 * u + 3, high[k]);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b32(as_u32(L[k]), ro, 2 * lo8[k], 0, kNonTemporal);
+            }
+            m2 = __builtin_elementwise_min(m2, (lv[k]) ? L[k] : as_u16x2(0xFFFFFFFFu));
         }
         __builtin_amdgcn_wave_barrier();
         if (PG) {
@@ -632,7 +711,7 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
                 const uint32_t lw = as_u32(L[k]);
                 const uint32_t i0 = lo8[k];
                 const uint32_t k0 = (lw << 16) | i0, k1 = (lw & 0xFFFF0000u) | (i0 + 1);
-                const bool ok = all_valid || lv[k];
+                const bool ok = lv[k];
                 key = ok && k0 < key ? k0 : key;
                 key = ok && k1 < key ? k1 : key;
             }
@@ -641,7 +720,11 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
             const int bi = (int)(key & 0xFFFFu);
             int f = 0;
             while (f + 1 < F && bi >= a.foff[f + 1]) ++f;
-            const int g = (WIN ? op[f] : 0) + (bi - a.foff[f]);
+            int of = 0;
+#pragma unroll
+            for (int ff = 0; ff < NF; ++ff)
+                if (WIN && ff == f) of = __builtin_amdgcn_readlane(c_off[ff], u);
+            const int g = of + (bi - a.foff[f]);
             double cf = c_cur[0], rf = r_cur[0];
 #pragma unroll
             for (int ff = 1; ff < NF; ++ff) {
@@ -661,12 +744,21 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
                 r_prev[ff] = r_cur[ff];
             }
         } else {
-            const uint32_t mw = as_u32(m2);
-            const uint32_t lo = mw & 0xFFFFu, hi = mw >> 16;
-            Mq = wave_min_u32(lo < hi ? lo : hi);
+            // (one pair a lane: the select stands between the halves' minimum
+            // and the reduction)
+            const uint32_t m = min_of_halves<KP == 1>(as_u32(KP == 1 ? L[0] : m2));
+            Mq = wave_min_u32(KP > 1 || lv[0] ? m : 0xFFFFu);
         }
+    };
+
+    // the 9th bits of the block at t0
+    auto store_high = [&](int t0) {
+        const int t = t0 + (lane >> 2);
+        if (lane >= 4 * PF || t >= len) return;
+        const long p = p0 + (long)t * pstride;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) oq[f] = op[f];
+        for (int k = 0; k < KP; ++k)
+            __builtin_nontemporal_store(high[k], bits + ((size_t)p * KP + k) * 4 + (lane & 3));
     };
 
     // Whole blocks of PF steps, then the tail.  The loop body is one
@@ -678,12 +770,14 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
         issue_block(t0 + PF, raw);
 #pragma unroll
         for (int u = 0; u < PF; ++u) step(t0 + u, u, false);
+        if (NARROW) store_high(t0);
         finish_block(t0 + PF, raw);
     }
     for (; t0 + PF <= len; t0 += PF) {
         issue_block(t0 + PF, raw);
 #pragma unroll
         for (int u = 0; u < PF; ++u) step(t0 + u, u, true);
+        if (NARROW) store_high(t0);
         finish_block(t0 + PF, raw);
     }
 #pragma unroll
@@ -691,11 +785,12 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
         if (t0 + u >= len) break;
         step(t0 + u, u, true);
     }
+    if (NARROW) store_high(t0);
 }
 
-template <int KP, int NF, bool WIN, bool SN, bool PG>
+template <int KP, int NF, bool WIN, bool SN, bool PG, bool NARROW>
 __global__ __launch_bounds__(64 * WAVES) void k_sgm_pk(const SgmArgs a) {
-    __shared__ uint32_t lbuf[WAVES][2][PK_LW];
+    __shared__ PkLds lbuf[WAVES];
     __shared__ int s_lut[256];   // P2 by intensity change
     extern __shared__ PgPlane planes[];   // path gradient: the level's plane lists (a.sumG entries)
     for (int i = threadIdx.x; i < 256; i += 64 * WAVES) s_lut[i] = a.lut[i];
@@ -705,7 +800,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_sgm_pk(const SgmArgs a) {
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int path = blockIdx.x * WAVES + wid;
     if (path >= a.path_begin[a.n_dirs]) return;
-    sgm_pk_path<KP, NF, WIN, SN, PG>(a, path, s_lut, planes, lbuf[wid][0], lbuf[wid][1]);
+    sgm_pk_path<KP, NF, WIN, SN, PG, NARROW>(a, path, s_lut, planes, lbuf[wid]);
 }
 
 // The fields the aggregation reads of a frame's arguments in device memory,
@@ -744,7 +839,7 @@ template <int KP, int NF, bool WIN, bool SN>
 __global__ __launch_bounds__(64 * WAVES) void k_sgm_pk_jobs(const SgmArgs *__restrict__ list,
                                                             const int *__restrict__ prefix, int n,
                                                             unsigned *__restrict__ counter) {
-    __shared__ uint32_t lbuf[WAVES][2][PK_LW];
+    __shared__ PkLds lbuf[WAVES];
     __shared__ int s_lut[WAVES][256];
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -762,8 +857,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_sgm_pk_jobs(const SgmArgs *__res
             __builtin_amdgcn_wave_barrier();
             cur = f;
         }
-        sgm_pk_path<KP, NF, WIN, SN, false>(uniform_sgm_args(list + f), job - rfl(prefix[f]), s_lut[wid], nullptr,
-                                            lbuf[wid][0], lbuf[wid][1]);
+        sgm_pk_path<KP, NF, WIN, SN, false, false>(uniform_sgm_args(list + f), job - rfl(prefix[f]), s_lut[wid], nullptr,
+                                            lbuf[wid]);
     }
 }
 
@@ -772,15 +867,19 @@ __global__ __launch_bounds__(64 * WAVES) void k_sgm_pk_jobs(const SgmArgs *__res
 template <int KP>
 void sgm_launch_pk(const SgmArgs &a, bool win, bool sn, dim3 grid, hipStream_t s) {
     const size_t lds = a.pg ? (size_t)a.sumG * sizeof(PgPlane) : 0;
-#define FMVS_SGMPK(W_, S_, P_)                                                                     \
-    if (win == W_ && sn == S_ && (a.pg != 0) == P_) {                                              \
-        if (a.n_fam == 1)                                                                          \
-            hipLaunchKernelGGL((k_sgm_pk<KP, 1, W_, S_, P_>), grid, dim3(64 * WAVES), lds, s, a);    \
-        else if (a.n_fam <= 4)                                                                     \
-            hipLaunchKernelGGL((k_sgm_pk<KP, 4, W_, S_, P_>), grid, dim3(64 * WAVES), lds, s, a);    \
-        else                                                                                       \
-            hipLaunchKernelGGL((k_sgm_pk<KP, kMaxFam, W_, S_, P_>), grid, dim3(64 * WAVES), lds, s, a); \
-        return;                                                                                    \
+#define FMVS_SGMPK(W_, S_, P_)                                                                                 \
+    if (win == W_ && sn == S_ && (a.pg != 0) == P_) {                                                         \
+        if (a.n_fam == 1 && a.narrow)                                                                         \
+            hipLaunchKernelGGL((k_sgm_pk<KP, 1, W_, S_, P_, !P_>), grid, dim3(64 * WAVES), lds, s, a);        \
+        else if (a.n_fam == 1)                                                                                \
+            hipLaunchKernelGGL((k_sgm_pk<KP, 1, W_, S_, P_, false>), grid, dim3(64 * WAVES), lds, s, a);       \
+        else if (a.n_fam <= 4 && a.narrow)                                                                    \
+            hipLaunchKernelGGL((k_sgm_pk<KP, 4, W_, S_, P_, !P_>), grid, dim3(64 * WAVES), lds, s, a);        \
+        else if (a.n_fam <= 4)                                                                                \
+            hipLaunchKernelGGL((k_sgm_pk<KP, 4, W_, S_, P_, false>), grid, dim3(64 * WAVES), lds, s, a);       \
+        else                                                                                                  \
+            hipLaunchKernelGGL((k_sgm_pk<KP, kMaxFam, W_, S_, P_, false>), grid, dim3(64 * WAVES), lds, s, a); \
+        return;                                                                                               \
     }
     FMVS_SGMPK(false, false, false)
     FMVS_SGMPK(true, false, false)

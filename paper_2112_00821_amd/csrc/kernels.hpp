@@ -65,6 +65,9 @@ struct SgmArgs {
     int dirs[8];
     uint16_t *out[8];         // [h][w][D] per launched direction (write mode)
     int path_begin[9];        // prefix sum of path counts over the launched directions
+    // path costs as 9-bit heights above S (see sgm_narrow); both the
+    // directions and the winner's pass have to agree
+    int narrow;
     // path-gradient offsets (SGM^Pi-pg): level plane lists and geometry
     int pg;
     int sumG;
@@ -81,6 +84,11 @@ struct SgmArgs {
     uint16_t *c3;             // [h][w][3]
 };
 int sgm_paths(int dir, int w, int h);
+// Whether the path costs of these arguments (shape, families, penalties, path
+// gradient) are held narrow in a frame of its own.
+bool sgm_narrow(const SgmArgs &a);
+// Narrow path costs of one direction as 16-bit ones: dst[h][w][D].
+hipError_t launch_widen(const uint8_t *S, const void *narrow, int w, int h, int D, uint16_t *dst, hipStream_t s);
 hipError_t launch_sgm(const SgmArgs &a, hipStream_t s);
 // several frames' aggregation in one persistent launch (see k_sgm.hip)
 size_t sgm_batch_bytes(int n);

@@ -90,6 +90,7 @@ struct LevelPlan {
     int G[kMaxFam], W[kMaxFam], foff[kMaxFam], goff[kMaxFam];
     double step[kMaxFam];   // inverse-distance step (lists uniform in 1/delta; path-gradient SGM)
     bool windows = false, sn = false;
+    bool narrow = false;   // path costs held narrow (sgm_narrow; not in a batch)
     size_t h_off = 0;   // offset (doubles) of this level's homographies in the parameter blob
     size_t d_off = 0;   // offset (doubles) of this level's plane lists
     size_t i_off = 0;   // offset (doubles) of their inverse distances
@@ -695,11 +696,24 @@ fassmvs_status make_plan(fassmvs_handle *h, const fassmvs_image *ref, const fass
         if (D > FASSMVS_MAX_LABELS) return fail(h, FASSMVS_EUNSUPPORTED, "more than 512 labels per pixel at a level");
         L.D = D;
         L.sumG = sumG;
+        {
+            SgmArgs a;
+            std::memset(&a, 0, sizeof(a));
+            a.w = L.w;
+            a.h = L.h;
+            a.D = D;
+            a.pg = c.sgm_variant == 2;
+            a.n_fam = F;
+            for (int f = 0; f < F; ++f) a.W[f] = L.W[f];
+            std::copy(P.lut, P.lut + 256, a.lut);
+            L.narrow = !c.sgm_debug && sgm_narrow(a);
+        }
         L.h_off = hsz;
         hsz += (size_t)n_views * sumG * 9;
         P.work_hyp += (double)L.w * L.h * D;
         P.work_hyp_views += (double)L.w * L.h * D * n_views;
-        // S read once per path, each path's u16 costs written once and read once
+        // S read once per path, each path's costs written once and read once (as
+        // u16, however they are held)
         P.sgm_bytes += (double)L.w * L.h * D * (c.n_paths * (1.0 + 2.0 + 2.0));
     }
     for (int l = 0; l < c.n_levels; ++l) {
@@ -855,7 +869,8 @@ struct PgGeom {
 
 fassmvs_status run_sgm(fassmvs_handle *h, const LevelPlan &L, const uint8_t *S, const int32_t *offs,
                        const int8_t *dI, const uint8_t *ref, int p1, const int *lut, int n_paths, uint16_t *const *bufs,
-                       uint16_t *Sbar, uint16_t *wta, uint16_t *c3, const PgGeom *pgg = nullptr) {
+                       uint16_t *Sbar, uint16_t *wta, uint16_t *c3, const PgGeom *pgg = nullptr,
+                       bool narrow = false) {
     SgmArgs a;
     std::memset(&a, 0, sizeof(a));
     if (pgg) {
@@ -884,6 +899,7 @@ fassmvs_status run_sgm(fassmvs_handle *h, const LevelPlan &L, const uint8_t *S, 
     a.ref = ref;
     a.p1 = p1;
     for (int i = 0; i < 256; ++i) a.lut[i] = lut[i];
+    a.narrow = narrow;
     {
         Timer t(h, ST_SGM_DIRS);
         a.n_dirs = n_paths;
@@ -1232,7 +1248,7 @@ fassmvs_status enqueue_frame(fassmvs_handle *h, const FramePlan &P) {
         PgGeom pgg{(const double *)h->params.p + L.d_off, P.fam_n};
         st = run_sgm(h, L, sa.S, sa.offs, sa.dI, sa.ref, P.p1, P.lut, c.n_paths, bufs,
                      c.sgm_debug ? (uint16_t *)h->sbar.p : nullptr, (uint16_t *)h->wta.p, (uint16_t *)h->c3.p,
-                     c.sgm_variant == 2 ? &pgg : nullptr);
+                     c.sgm_variant == 2 ? &pgg : nullptr, L.narrow);
         if (st != FASSMVS_OK) return st;
         if ((st = enqueue_post(h, P, l)) != FASSMVS_OK) return st;
     }
@@ -1297,8 +1313,8 @@ std::string plan_signature(const FramePlan &P) {
         raw(L.W, sizeof(int) * L.F);
         raw(L.step, sizeof(double) * L.F);
         raw(L.Kinv, sizeof(L.Kinv));
-        const char flags[2] = {(char)L.windows, (char)L.sn};
-        raw(flags, 2);
+        const char flags[3] = {(char)L.windows, (char)L.sn, (char)L.narrow};
+        raw(flags, 3);
         raw(&L.h_off, sizeof(size_t));
         raw(&L.d_off, sizeof(size_t));
         raw(&L.i_off, sizeof(size_t));
@@ -2429,6 +2445,22 @@ fassmvs_status fassmvs_level_map(fassmvs_handle *h, int32_t level, int32_t what,
                 // path costs of direction r (each direction has its own buffer)
                 src = h->sgmbuf[what - 10].p;
                 bytes = N * L.D * 2;
+                if (L.narrow && h->S.bytes >= N * L.D && h->sgmbuf[what - 10].bytes >= bytes) {
+                    if (dst_bytes < bytes) return fail(h, FASSMVS_EINVAL, "destination too small");
+                    // straight into a device buffer, else through one
+                    hipPointerAttribute_t at;
+                    const bool direct = hipPointerGetAttributes(&at, dst) == hipSuccess && at.type == hipMemoryTypeDevice;
+                    if (!direct) (void)hipGetLastError();
+                    void *wide = dst;
+                    if (!direct) HIPCHK(h, hipMalloc(&wide, bytes), "level map copy");
+                    hipError_t e = launch_widen((const uint8_t *)h->S.p, src, L.w, L.h, L.D, (uint16_t *)wide, h->stream);
+                    if (e == hipSuccess && !direct)
+                        e = hipMemcpyAsync(dst, wide, bytes, hipMemcpyDeviceToDevice, h->stream);
+                    const hipError_t e2 = hipStreamSynchronize(h->stream);
+                    if (!direct) hipFree(wide);
+                    HIPCHK(h, e == hipSuccess ? e2 : e, "level map copy");
+                    return FASSMVS_OK;
+                }
                 break;
             }
             if (what >= 30 && what <= 30 + P.n_views) {
@@ -2606,6 +2638,8 @@ fassmvs_status stage_cost_any(fassmvs_handle *h, int cost, int32_t w, int32_t hg
     hipError_t e = hipSuccess;
     uint32_t *quads = nullptr;   // the views' packed texels, held for this call only
     if (!warped) {
+        // (the sweep's texel offsets are 32-bit bytes of 4-byte texels)
+        if ((size_t)w * hgt >= (size_t)1 << 30) return fail(h, FASSMVS_EUNSUPPORTED, "view too large");
         if ((e = hipMalloc((void **)&quads, (size_t)n_views * w * hgt * 4)) != hipSuccess) {
             (void)hipGetLastError();
             return fail(h, FASSMVS_ENOMEM, std::string("device allocation failed: ") + hipGetErrorString(e));

@@ -74,3 +74,34 @@ def test_path_gradient_planes(orc, hd, w, h, W, G, tilt):
                         offs=hd.upload(offs), want_lr=True, want_sbar=True)
     assert np.array_equal(r["Lr"].numpy(), Lr)
     assert np.array_equal(r["Sbar"].numpy(), Sbar)
+
+
+@pytest.mark.parametrize("planes,paths,families", [(128, 4, 1), (136, 8, 1), (72, 8, 2), (127, 8, 1)])
+def test_large_frame_path_costs(planes, paths, families):
+    """A frame just over 2^27 labels, path costs held as 9 bits (or, with an
+    odd label count, as 16), against the same frame with every path's costs
+    kept as 16 bits: equal, as are the maps."""
+    import copy
+    import paper_2112_00821_amd as fm
+    import scenegen
+    wl = copy.deepcopy(scenegen.make_workload("config1"))
+    h, w = 1024, -(-(1 << 27) // (1024 * planes * families) // 64) * 64 + 64
+    grow = lambda im: np.ascontiguousarray(np.tile(im, (-(-h // im.shape[0]), -(-w // im.shape[1])))[:h, :w])
+    wl["ref"]["img"] = grow(wl["ref"]["img"])
+    for v in wl["views"]:
+        v["img"] = grow(v["img"])
+    wl["width"], wl["height"] = w, h
+    fams = []
+    for i in range(families):
+        fams.append(dict(wl["families"][0], count=planes, n=[np.sin(0.05 * i), 0.0, -np.cos(0.05 * i)]))
+    wl["families"] = fams
+    wl["params"].update(n_levels=1, n_paths=paths, p1=50, p2_mode=1)   # P2 up to 450
+    got = []
+    for debug in (0, 1):
+        with fm.Handle(fm.config_from_params(wl["params"], keep_levels=1, sgm_debug=debug)) as hd:
+            out = hd.run_frame(wl)
+            D = planes * families
+            got.append([hd.level_map(0, 10 + r, D=D) for r in range(paths)] + [hd.level_map(0, 4), out["depth"]])
+    assert got[1][0].max() > 255
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
