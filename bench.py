@@ -37,8 +37,20 @@ SWEEP_ALG_OPS_NCC5 = 3 * 25 + 20 + 15
 SGM_ALG_BYTES = 12.0
 # bytes of this design per (pixel, hypothesis): S read by each of the 8
 # direction walks (8 x 1 B), each direction's uint16 path costs written once
-# and read once by the streaming winner-takes-all (2 x 8 x 2 B)
+# and read once by the streaming winner-takes-all (2 x 8 x 2 B); levels of
+# 2^27 labels and more hold 9 bits in place of the uint16, and the
+# winner-takes-all reads S once more (8 + 2 x 8 x 9 / 8 + 1 B)
 SGM_DESIGN_BYTES = 40.0
+SGM_DESIGN_BYTES_NARROW = 27.0
+
+
+def sgm_design_bytes(wl, hyp):
+    """Design bytes per (pixel, hypothesis) of a level of hyp labels."""
+    p = wl["params"]
+    scale = 1 if p.get("cost") == "ncc" else max(wl["side"].count(-1), wl["side"].count(1))
+    p2 = p["p2_fixed"] if p["p2_mode"] == 0 else p["p1"] * (1.0 + p["p2_alpha"])
+    narrow = hyp >= 1 << 27 and scale * p2 < 511.5 and p["sgm_variant"] != 2
+    return SGM_DESIGN_BYTES_NARROW if narrow else SGM_DESIGN_BYTES
 PROFILE = os.path.join(ROOT, "profiles", "k_sweep_config2.md")
 SGM_PROFILE = os.path.join(ROOT, "profiles", "k_sgm_pk_config2.md")
 
@@ -129,7 +141,7 @@ def main():
         roof = {"bound": "hbm", "kernel": "k_sgm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": achieved / PEAK_HBM_GBS, "traffic": None, "stage_ms_per_frame": sgm_ms,
                 "alg_bytes_per_px_hyp": SGM_ALG_BYTES}
-    sgm_roof = sgm_roofline(m, args.steps)
+    sgm_roof = sgm_roofline(m, args.steps, wl)
     # counted HBM bytes per launch of the aggregation and WTA kernels, from
     # the committed profile while their sources are unchanged
     if args.workload == "config2":
@@ -236,17 +248,19 @@ def measure(fm, wl, steps, warmup, host_io_steps=0, calib_copy_mb=0):
     return res
 
 
-def sgm_roofline(m, steps):
+def sgm_roofline(m, steps, wl):
     """The aggregation's bandwidth over all levels and at full resolution
     only, by the method's bytes and by this design's."""
     hyp = m["work"]["pixel_hyp"]
     times, times0 = m["times"], m["times0"]
     sgm_ms = (times["sgm_dirs"][0] + times["sgm_wta"][0]) / steps
+    design = sum(sgm_design_bytes(wl, x) * x for x in m["work"]["pixel_hyp_level"]) / hyp
+    design0 = sgm_design_bytes(wl, m["work"]["pixel_hyp_level"][0])
     r = {"bound": "hbm", "stages": "sgm_dirs + sgm_wta", "ms_per_frame": sgm_ms, "peak": PEAK_HBM_GBS,
          "unit": "GB/s", "alg_bytes_per_px_hyp": SGM_ALG_BYTES,
          "achieved_alg": SGM_ALG_BYTES * hyp / (sgm_ms / 1e3) / 1e9,
-         "design_bytes_per_px_hyp": SGM_DESIGN_BYTES,
-         "achieved_design": SGM_DESIGN_BYTES * hyp / (sgm_ms / 1e3) / 1e9}
+         "design_bytes_per_px_hyp": round(design, 3),
+         "achieved_design": design * hyp / (sgm_ms / 1e3) / 1e9}
     r["frac_alg"] = r["achieved_alg"] / PEAK_HBM_GBS
     r["frac_design"] = r["achieved_design"] / PEAK_HBM_GBS
     # full resolution only (the coarser levels' volumes partly stay in cache)
@@ -258,8 +272,8 @@ def sgm_roofline(m, steps):
             "sgm_wta_ms": round(times0["sgm_wta"][0] / steps, 4), "pixel_hyp": hyp0,
             "achieved_alg": SGM_ALG_BYTES * hyp0 / (sgm0_ms / 1e3) / 1e9,
             "frac_alg": SGM_ALG_BYTES * hyp0 / (sgm0_ms / 1e3) / 1e9 / PEAK_HBM_GBS,
-            "design_bytes_per_px_hyp": SGM_DESIGN_BYTES,
-            "frac_design": SGM_DESIGN_BYTES * hyp0 / (sgm0_ms / 1e3) / 1e9 / PEAK_HBM_GBS}
+            "design_bytes_per_px_hyp": design0,
+            "frac_design": design0 * hyp0 / (sgm0_ms / 1e3) / 1e9 / PEAK_HBM_GBS}
     return r
 
 
@@ -273,7 +287,7 @@ def frame_section(fm, wl, steps):
             "value": round(hyp / 1e6 / (m["ms"] / 1e3), 1), "unit": "Mpx·hyp/s", "pixel_hyp_per_frame": hyp,
             "stage_ms_per_frame": {k: round(v[0] / steps, 4) for k, v in m["times"].items() if v[1]},
             "stage_ms_per_frame_level0": {k: round(v[0] / steps, 4) for k, v in m["times0"].items() if v[1]},
-            "sgm_roofline": sgm_roofline(m, steps)}
+            "sgm_roofline": sgm_roofline(m, steps, wl)}
 
 
 def _render_workload(name):
