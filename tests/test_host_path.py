@@ -1,0 +1,88 @@
+"""The library's host code over a fake HIP runtime (fake_hip.cpp: two devices
+in host memory, queued copies, kernels that do nothing), each test in a process
+of its own: where copies go, what is allocated, on which device, and what an
+error leaves behind."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes as C, sys
+fake = C.CDLL({so!r}, mode=C.RTLD_GLOBAL)
+for f in ("fake_held", "fake_peak", "fake_bytes_to_pageable", "fake_pending"):
+    getattr(fake, f).restype = C.c_size_t
+fake.fake_calls.restype = C.c_long
+fake.fake_calls.argtypes = [C.c_char_p]
+fake.fake_limit.argtypes = [C.c_size_t]
+fake.fake_fail_copy.argtypes = [C.c_long]
+fake.fake_pinned.restype = C.c_void_p
+fake.fake_pinned.argtypes = [C.c_size_t]
+sys.path[:0] = [{root!r}, {root!r} + "/tests"]
+import numpy as np
+import paper_2112_00821_amd as fm
+MB = 1 << 20
+L = fm.lib()
+"""
+
+
+@pytest.fixture(scope="module")
+def child(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(ROOT, "tests", "fake_hip.cpp"), "-o", so], check=True)
+
+    def run(code):
+        r = subprocess.run([sys.executable, "-c", PRELUDE.format(so=so, root=ROOT) + code], capture_output=True,
+                           text=True, timeout=120)
+        assert r.returncode == 0, (r.returncode, r.stdout[-2000:], r.stderr[-3000:])
+
+    return run
+
+
+def test_known_destinations_take_one_copy(child):
+    """Page-locked (and device) destinations: one copy by the runtime, straight
+    into them; ordinary memory beside them goes through the pinned slots."""
+    child("""
+n = 5 * MB + 3
+a = np.random.default_rng(1).integers(0, 256, n, dtype=np.uint8)
+with fm.Handle(fm.default_config()) as h:
+    d = h.upload(a)
+    pinned, dev = fake.fake_pinned(n), h.empty((n,), np.uint8)
+    for dst in (pinned, pinned, dev.ptr):
+        fake.fake_reset()
+        assert L.fassmvs_memcpy(h.h, dst, d.ptr, n, 1) == fm.OK
+        assert fake.fake_calls(b"hipMemcpyAsync") == 1
+        assert np.array_equal(np.ctypeslib.as_array((C.c_uint8 * n).from_address(dst)), a)
+    out = np.zeros(n, np.uint8)
+    fake.fake_reset()
+    assert L.fassmvs_memcpy(h.h, out.ctypes.data, d.ptr, n, 1) == fm.OK
+    assert np.array_equal(out, a) and fake.fake_bytes_to_pageable() == 0
+""")
+
+
+def test_frame_maps_to_mixed_memory(child):
+    """A frame's maps, one in page-locked and two in ordinary memory."""
+    child("""
+import scenegen
+wl = scenegen.make_workload("config2_small")
+h, w = wl["ref"]["img"].shape
+N = h * w
+for _ in range(4):     # over the size where the slots are used
+    wl["ref"]["img"] = np.tile(wl["ref"]["img"], (1, 2))
+    for v in wl["views"]:
+        v["img"] = np.tile(v["img"], (1, 2))
+    h, w = wl["ref"]["img"].shape
+with fm.Handle(fm.config_from_params(wl["params"])) as hd:
+    t = hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], wl["families"])
+    depth = fake.fake_pinned(h * w * 4)
+    normal, conf = np.empty((h, w, 3), np.float32), np.empty((h, w), np.float32)
+    fake.fake_reset()
+    assert L.fassmvs_poll(hd.h, t, depth, normal.ctypes.data, conf.ctypes.data, fm.MEM_HOST, -1) == fm.OK
+    assert fake.fake_pending() == 0 and fake.fake_bytes_to_pageable() == 0
+    chunks = sum(-(-b // (2 * MB)) for b in (h * w * 12, h * w * 4))
+    assert fake.fake_calls(b"hipMemcpyAsync") == 1 + chunks
+""")
