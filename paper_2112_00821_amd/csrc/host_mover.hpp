@@ -75,8 +75,9 @@ public:
     }
 
     // Device ranges to host memory, after the work already on the stream;
-    // returns when the bytes are there.  Ranges whose destination the runtime
-    // knows go straight there in one copy.
+    // returns when the bytes are there, on an error when no copy still runs.
+    // Ranges whose destination the runtime knows go straight there in one
+    // copy.
     hipError_t to_host(const std::vector<DeviceRange> &ranges, hipStream_t stream) {
         size_t total = 0;
         for (auto &r : ranges) total += r.bytes;
@@ -92,11 +93,12 @@ public:
             direct.insert(direct.end(), staged.begin(), staged.end());
             staged.clear();
         }
-        for (auto &r : direct) {
-            const hipError_t e = hipMemcpyAsync(r.dst, r.src, r.bytes, hipMemcpyDeviceToHost, stream);
-            if (e != hipSuccess) return e;
-        }
-        return staged.empty() ? hipStreamSynchronize(stream) : through_slots(staged, stream);
+        hipError_t e = hipSuccess;
+        for (size_t i = 0; i < direct.size() && e == hipSuccess; ++i)
+            e = hipMemcpyAsync(direct[i].dst, direct[i].src, direct[i].bytes, hipMemcpyDeviceToHost, stream);
+        if (e == hipSuccess && !staged.empty()) e = through_slots(staged, stream);
+        const hipError_t es = hipStreamSynchronize(stream);
+        return e == hipSuccess ? es : e;
     }
 
     static constexpr size_t kPiece = 128 << 10;
@@ -118,6 +120,7 @@ private:
         return true;
     }
 
+    // (after an error copies into the slots may still run)
     hipError_t through_slots(const std::vector<DeviceRange> &ranges, hipStream_t stream) {
         std::vector<DeviceRange> chunks;
         for (auto &r : ranges)
@@ -144,7 +147,6 @@ private:
                 if (sent < n) e = send(sent++);
             }
         }
-        if (e != hipSuccess) (void)hipStreamSynchronize(stream);   // nothing may still write to the slots
         return e;
     }
 

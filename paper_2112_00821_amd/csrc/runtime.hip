@@ -1363,8 +1363,11 @@ fassmvs_status copy_maps(fassmvs_handle *h, fassmvs_handle *from, size_t N, floa
     if (mem_kind == FASSMVS_MEM_HOST) {
         HIPCHK(h, h->mover.to_host(maps, h->stream), "output copy");
     } else {
-        for (auto &m : maps)
-            HIPCHK(h, hipMemcpyAsync(m.dst, m.src, m.bytes, hipMemcpyDeviceToDevice, h->stream), "output copy");
+        hipError_t e = hipSuccess;
+        for (size_t i = 0; i < maps.size() && e == hipSuccess; ++i)
+            e = hipMemcpyAsync(maps[i].dst, maps[i].src, maps[i].bytes, hipMemcpyDeviceToDevice, h->stream);
+        const hipError_t es = hipStreamSynchronize(h->stream);   // on an error too: no copy still runs
+        HIPCHK(h, e == hipSuccess ? es : e, "output copy");
     }
     return FASSMVS_OK;
 }
@@ -2132,11 +2135,7 @@ fassmvs_status fassmvs_poll_batch(fassmvs_handle *h, uint64_t ticket, int32_t in
         h->batch_busy = false;
     }
     fassmvs_handle *ch = h->children[index];
-    const fassmvs_status st =
-        copy_maps(h, ch, (size_t)ch->plan.w * ch->plan.h, depth, normal, confidence, mem_kind);
-    if (st != FASSMVS_OK) return st;
-    HIPCHK(h, hipStreamSynchronize(h->stream), "output copy");
-    return FASSMVS_OK;
+    return copy_maps(h, ch, (size_t)ch->plan.w * ch->plan.h, depth, normal, confidence, mem_kind);
 }
 
 fassmvs_status fassmvs_batch_tuning(fassmvs_handle *h, int32_t *rows_per_thread, int32_t *sweep_blocks,
@@ -2286,7 +2285,8 @@ fassmvs_status fassmvs_poll(fassmvs_handle *h, uint64_t ticket, float *depth, fl
             copy_maps(h, h, (size_t)h->out_w * h->out_h, depth, normal, confidence, mem_kind);
         if (st != FASSMVS_OK) return st;
     }
-    HIPCHK(h, hipStreamSynchronize(h->stream), "output copy");
+    // the maps are there; the timers' last event may not be
+    if (h->cfg.profile) HIPCHK(h, hipStreamSynchronize(h->stream), "output copy");
     collect_timers(h);
     h->last_work[0] = h->plan.work_hyp;
     h->last_work[1] = h->plan.work_hyp_views;

@@ -625,7 +625,8 @@ fassmvs_status fassmvs_server_fetch(fassmvs_server *s, uint64_t request_id, floa
     } else {
         for (auto &m : maps)
             if (e == hipSuccess) e = hipMemcpyAsync(m.dst, m.src, m.bytes, hipMemcpyDeviceToDevice, s->fetch);
-        if (e == hipSuccess) e = hipStreamSynchronize(s->fetch);
+        const hipError_t es = hipStreamSynchronize(s->fetch);   // on an error too: no copy still runs
+        if (e == hipSuccess) e = es;
     }
     give_maps(r);
     return e == hipSuccess ? FASSMVS_OK : sfail(s, FASSMVS_EDEVICE, "result copy failed");

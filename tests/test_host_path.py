@@ -86,3 +86,57 @@ with fm.Handle(fm.config_from_params(wl["params"])) as hd:
     chunks = sum(-(-b // (2 * MB)) for b in (h * w * 12, h * w * 4))
     assert fake.fake_calls(b"hipMemcpyAsync") == 1 + chunks
 """)
+
+
+@pytest.mark.parametrize("mem_kind", ["MEM_HOST", "MEM_DEVICE"])
+@pytest.mark.parametrize("large", [False, True])
+def test_failed_copy_leaves_none_running(child, mem_kind, large):
+    """A map's copy fails: when the call returns, no earlier one is still to
+    write into the caller's memory."""
+    child(f"large, mem_kind = {large}, fm.{mem_kind}" + """
+import scenegen
+wl = scenegen.make_workload("config1")
+if large:
+    for im in (wl["ref"], *wl["views"]):
+        im["img"] = np.tile(im["img"], (4, 4))
+h, w = wl["ref"]["img"].shape
+for ok in (1, 2):
+    with fm.Handle(fm.config_from_params(wl["params"])) as hd:
+        t = hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], wl["families"])
+        if mem_kind == fm.MEM_DEVICE:
+            maps = [hd.empty((h * w * c,), np.float32).ptr for c in (1, 3, 1)]
+        else:
+            maps = [fake.fake_pinned(h * w * c * 4) for c in (1, 3, 1)]
+        hd.synchronize()
+        fake.fake_fail_copy(ok)
+        assert L.fassmvs_poll(hd.h, t, *maps, mem_kind, -1) == fm.EDEVICE
+        pending = fake.fake_pending()
+        fake.fake_fail_copy(-1)
+        assert pending == 0, pending
+""")
+
+
+def test_failed_fetch_leaves_no_copy_running(child):
+    """The same where the server hands results out (their buffers go back to
+    its pool)."""
+    child("""
+import scenegen
+wl = scenegen.make_workload("config1")
+h, w = wl["ref"]["img"].shape
+for kind in (fm.MEM_HOST, fm.MEM_DEVICE):
+    s = fm.Server(fm.config_from_params(wl["params"]), n_slots=1)
+    sid = s.open_stream(wl["K"], w, h, wl["families"], max_keyframes=2, min_baseline=0.0)
+    for i, v in enumerate((*wl["views"], wl["ref"])):
+        s.submit(sid, v["img"], v["R"], v["t"])
+        r = s.next()
+    assert r["status"] == fm.OK, r
+    with fm.Handle(fm.default_config()) as hd:
+        dst = [hd.empty((h * w * c,), np.float32) for c in (1, 3, 1)]
+        before = fake.fake_pending()
+        fake.fake_fail_copy(2)
+        st = L.fassmvs_server_fetch(s.s, r["request_id"], *[d.ptr for d in dst], kind)
+        pending = fake.fake_pending() - before
+        fake.fake_fail_copy(-1)
+        assert st == fm.EDEVICE and pending == 0, (st, pending)
+    s.close()
+""")
