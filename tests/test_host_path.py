@@ -104,7 +104,8 @@ for ok in (1, 2):
     with fm.Handle(fm.config_from_params(wl["params"])) as hd:
         t = hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], wl["families"])
         if mem_kind == fm.MEM_DEVICE:
-            maps = [hd.empty((h * w * c,), np.float32).ptr for c in (1, 3, 1)]
+            held = [hd.empty((h * w * c,), np.float32) for c in (1, 3, 1)]
+            maps = [d.ptr for d in held]
         else:
             maps = [fake.fake_pinned(h * w * c * 4) for c in (1, 3, 1)]
         hd.synchronize()
