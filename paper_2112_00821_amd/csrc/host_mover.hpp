@@ -22,7 +22,6 @@
 #include <cstdint>
 #include <cstring>
 #include <mutex>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -42,6 +41,15 @@ struct DeviceRange {
     void *dst;
     const void *src;
     size_t bytes;
+};
+
+// A frame's maps, or one transfer (in place: copies need no host memory).
+struct DeviceRanges {
+    DeviceRange r[3];
+    size_t n = 0;
+    void add(void *dst, const void *src, size_t bytes) {
+        if (dst && bytes) r[n++] = DeviceRange{dst, src, bytes};
+    }
 };
 
 class HostMover {
@@ -71,32 +79,36 @@ public:
             return;
         }
         Session s(*this);
-        share(pieces);
+        share(pieces.data(), pieces.size());
     }
 
     // Device ranges to host memory, after the work already on the stream;
     // returns when the bytes are there, on an error when no copy still runs.
     // Ranges whose destination the runtime knows go straight there in one
     // copy.
-    hipError_t to_host(const std::vector<DeviceRange> &ranges, hipStream_t stream) {
+    hipError_t to_host(const DeviceRanges &ranges, hipStream_t stream) {
         size_t total = 0;
-        for (auto &r : ranges) total += r.bytes;
+        for (size_t i = 0; i < ranges.n; ++i) total += ranges.r[i].bytes;
         if (total == 0) return hipSuccess;
-        std::vector<DeviceRange> direct, staged;
-        total = 0;
-        for (auto &r : ranges) {
-            const bool own = r.bytes != 0 && pageable(r.dst);
-            (own ? staged : direct).push_back(r);
-            total += own ? r.bytes : 0;
+        DeviceRanges staged;
+        bool direct[3] = {true, true, true};
+        if (total >= kShare) {
+            total = 0;
+            for (size_t i = 0; i < ranges.n; ++i) {
+                const DeviceRange &r = ranges.r[i];
+                if (!pageable(r.dst)) continue;
+                direct[i] = false;
+                staged.add(r.dst, r.src, r.bytes);
+                total += r.bytes;
+            }
         }
-        if (total < kShare || !slots()) {
-            direct.insert(direct.end(), staged.begin(), staged.end());
-            staged.clear();
-        }
+        const bool slotted = total >= kShare && staged.n > 0 && slots();
         hipError_t e = hipSuccess;
-        for (size_t i = 0; i < direct.size() && e == hipSuccess; ++i)
-            e = hipMemcpyAsync(direct[i].dst, direct[i].src, direct[i].bytes, hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess && !staged.empty()) e = through_slots(staged, stream);
+        for (size_t i = 0; i < ranges.n && e == hipSuccess; ++i) {
+            const DeviceRange &r = ranges.r[i];
+            if (direct[i] || !slotted) e = hipMemcpyAsync(r.dst, r.src, r.bytes, hipMemcpyDeviceToHost, stream);
+        }
+        if (e == hipSuccess && slotted) e = through_slots(staged, stream);
         const hipError_t es = hipStreamSynchronize(stream);
         return e == hipSuccess ? es : e;
     }
@@ -109,7 +121,7 @@ private:
     static constexpr size_t kSlot = 2 << 20, kSlots = 2, kShare = 1 << 20;
     static constexpr int kHelpers = 5;   // 3: 37 GB/s, 5: 39, 7: the same
 
-    uint8_t *slot(size_t i) { return pin_ + (i % kSlots) * kSlot; }
+    uint8_t *slot(size_t k) { return pin_ + k * kSlot; }
 
     // Whether p is ordinary host memory: neither page-locked nor device
     // memory, which one copy by the runtime reaches at link rate.
@@ -121,31 +133,34 @@ private:
     }
 
     // (after an error copies into the slots may still run)
-    hipError_t through_slots(const std::vector<DeviceRange> &ranges, hipStream_t stream) {
-        std::vector<DeviceRange> chunks;
-        for (auto &r : ranges)
-            for (size_t o = 0; o < r.bytes; o += kSlot)
-                chunks.push_back({(uint8_t *)r.dst + o, (const uint8_t *)r.src + o, std::min(kSlot, r.bytes - o)});
-        const size_t n = chunks.size();
-        auto send = [&](size_t i) {
-            hipError_t e = hipMemcpyAsync(slot(i), chunks[i].src, chunks[i].bytes, hipMemcpyDeviceToHost, stream);
-            return e == hipSuccess ? hipEventRecord(events_[i % kSlots], stream) : e;
+    hipError_t through_slots(const DeviceRanges &ranges, hipStream_t stream) {
+        DeviceRange in[kSlots];   // what each slot receives
+        size_t at = 0, off = 0, sent = 0;
+        auto send = [&] {   // the next chunk
+            const DeviceRange &r = ranges.r[at];
+            const size_t k = sent++ % kSlots, bytes = std::min(kSlot, r.bytes - off);
+            in[k] = DeviceRange{(uint8_t *)r.dst + off, (const uint8_t *)r.src + off, bytes};
+            off += bytes;
+            if (off == r.bytes) {
+                ++at;
+                off = 0;
+            }
+            const hipError_t e = hipMemcpyAsync(slot(k), in[k].src, bytes, hipMemcpyDeviceToHost, stream);
+            return e == hipSuccess ? hipEventRecord(events_[k], stream) : e;
         };
         hipError_t e = hipSuccess;
-        size_t sent = 0;
-        for (; sent < std::min(n, kSlots) && e == hipSuccess; ++sent) e = send(sent);
-        if (e == hipSuccess) {
-            Session s(*this);
-            std::vector<HostPiece> pieces;
-            for (size_t i = 0; i < n && e == hipSuccess; ++i) {
-                if ((e = hipEventSynchronize(events_[i % kSlots])) != hipSuccess) break;
-                pieces.clear();
-                for (size_t o = 0; o < chunks[i].bytes; o += kPiece)
-                    pieces.push_back({(uint8_t *)chunks[i].dst + o, slot(i) + o,
-                                      std::min(kPiece, chunks[i].bytes - o), 1, 0, 0});
-                share(pieces);
-                if (sent < n) e = send(sent++);
-            }
+        while (e == hipSuccess && sent < kSlots && at < ranges.n) e = send();
+        if (e != hipSuccess) return e;
+        Session s(*this);
+        for (size_t i = 0; i < sent && e == hipSuccess; ++i) {
+            const size_t k = i % kSlots;
+            if ((e = hipEventSynchronize(events_[k])) != hipSuccess) break;
+            HostPiece pieces[kSlot / kPiece];
+            size_t n = 0;
+            for (size_t o = 0; o < in[k].bytes; o += kPiece)
+                pieces[n++] = HostPiece{(uint8_t *)in[k].dst + o, slot(k) + o, std::min(kPiece, in[k].bytes - o), 1, 0, 0};
+            share(pieces, n);
+            if (at < ranges.n) e = send();
         }
         return e;
     }
@@ -175,7 +190,7 @@ private:
             const int want = std::min(kHelpers, (int)std::thread::hardware_concurrency() / 2);
             try {
                 while ((int)m.threads_.size() < want) m.threads_.emplace_back([&mm] { mm.help(); });
-            } catch (const std::system_error &) {
+            } catch (...) {   // no thread, or no memory for one: with fewer
             }
             {
                 std::lock_guard<std::mutex> lk(m.m_);
@@ -191,14 +206,14 @@ private:
     // count_, and count_ before pieces_; here they are set in that order and
     // count_ is 0 between batches, so what it reads belongs to one batch or
     // its exchange fails.
-    void share(const std::vector<HostPiece> &pieces) {
-        if (pieces.empty()) return;
+    void share(const HostPiece *pieces, size_t n) {
+        if (n == 0) return;
         state_.store(((state_.load() >> 32) + 1) << 32);
         done_.store(0);
-        pieces_.store(pieces.data());
-        count_.store((uint32_t)pieces.size());
+        pieces_.store(pieces);
+        count_.store((uint32_t)n);
         work();
-        while (done_.load() < pieces.size()) pause();
+        while (done_.load() < n) pause();
         count_.store(0);
     }
 

@@ -1356,16 +1356,16 @@ fassmvs_status enqueue_frame_graph(fassmvs_handle *h, const FramePlan &P) {
 fassmvs_status copy_maps(fassmvs_handle *h, fassmvs_handle *from, size_t N, float *depth, float *normal, float *conf,
                          int mem_kind) {
     const auto &B = from->lb[0];
-    std::vector<DeviceRange> maps;
-    if (depth) maps.push_back({depth, B.depth.p, N * 4});
-    if (normal) maps.push_back({normal, B.normal.p, N * 12});
-    if (conf) maps.push_back({conf, B.conf.p, N * 4});
+    DeviceRanges maps;
+    maps.add(depth, B.depth.p, N * 4);
+    maps.add(normal, B.normal.p, N * 12);
+    maps.add(conf, B.conf.p, N * 4);
     if (mem_kind == FASSMVS_MEM_HOST) {
         HIPCHK(h, h->mover.to_host(maps, h->stream), "output copy");
     } else {
         hipError_t e = hipSuccess;
-        for (size_t i = 0; i < maps.size() && e == hipSuccess; ++i)
-            e = hipMemcpyAsync(maps[i].dst, maps[i].src, maps[i].bytes, hipMemcpyDeviceToDevice, h->stream);
+        for (size_t i = 0; i < maps.n && e == hipSuccess; ++i)
+            e = hipMemcpyAsync(maps.r[i].dst, maps.r[i].src, maps.r[i].bytes, hipMemcpyDeviceToDevice, h->stream);
         const hipError_t es = hipStreamSynchronize(h->stream);   // on an error too: no copy still runs
         HIPCHK(h, e == hipSuccess ? es : e, "output copy");
     }
@@ -2519,7 +2519,9 @@ fassmvs_status fassmvs_memcpy(fassmvs_handle *h, void *dst, const void *src, siz
                            bytes / 16);
         HIPCHK(h, hipGetLastError(), "copy launch");
     } else if (kind == 1 && bytes >= ((size_t)1 << 20)) {
-        HIPCHK(h, h->mover.to_host({{dst, src, bytes}}, h->stream), "copy");
+        DeviceRanges range;
+        range.add(dst, src, bytes);
+        HIPCHK(h, h->mover.to_host(range, h->stream), "copy");
     } else {
         HIPCHK(h, hipMemcpyAsync(dst, src, bytes, k[kind], h->stream), "copy");
     }

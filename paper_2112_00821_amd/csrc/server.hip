@@ -614,17 +614,17 @@ fassmvs_status fassmvs_server_fetch(fassmvs_server *s, uint64_t request_id, floa
     // copies on the server's own non-blocking stream: they wait for nothing
     // but themselves, frames in flight keep running
     std::lock_guard<std::mutex> flk(s->fetch_mu);
-    std::vector<fmvs::DeviceRange> maps;
-    if (depth) maps.push_back({depth, r.depth, N * 4});
-    if (normal) maps.push_back({normal, r.normal, N * 12});
-    if (confidence) maps.push_back({confidence, r.conf, N * 4});
+    fmvs::DeviceRanges maps;
+    maps.add(depth, r.depth, N * 4);
+    maps.add(normal, r.normal, N * 12);
+    maps.add(confidence, r.conf, N * 4);
     hipError_t e = hipSuccess;
     if (mem_kind == FASSMVS_MEM_HOST) {
         e = hipSetDevice(s->cfg.device);
         if (e == hipSuccess) e = s->mover.to_host(maps, s->fetch);
     } else {
-        for (auto &m : maps)
-            if (e == hipSuccess) e = hipMemcpyAsync(m.dst, m.src, m.bytes, hipMemcpyDeviceToDevice, s->fetch);
+        for (size_t i = 0; i < maps.n && e == hipSuccess; ++i)
+            e = hipMemcpyAsync(maps.r[i].dst, maps.r[i].src, maps.r[i].bytes, hipMemcpyDeviceToDevice, s->fetch);
         const hipError_t es = hipStreamSynchronize(s->fetch);   // on an error too: no copy still runs
         if (e == hipSuccess) e = es;
     }

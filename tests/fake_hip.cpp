@@ -7,16 +7,25 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
 namespace {
 std::mutex mu;
+std::atomic<bool> no_memory{false};
+thread_local int inside = 0;   // this runtime's own allocations always succeed
+struct Lock {
+    std::lock_guard<std::mutex> lk{mu};
+    Lock() { ++inside; }
+    ~Lock() { --inside; }
+};
 struct Mem {
     size_t bytes;
     bool device;
@@ -48,7 +57,7 @@ void note(const char *name, bool device_call = false) {
     if (device_call && expected >= 0 && current != expected) on_wrong = true;
 }
 hipError_t get(void **p, size_t n, bool device, const char *name) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     note(name, true);
     *p = nullptr;
     if (device && (n > limit || held > limit - n)) return hipErrorOutOfMemory;
@@ -58,7 +67,7 @@ hipError_t get(void **p, size_t n, bool device, const char *name) {
     return hipSuccess;
 }
 hipError_t drop(void *p, const char *name) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     note(name);
     if (!p) return hipSuccess;
     auto it = mems.find((uintptr_t)p);
@@ -74,14 +83,22 @@ void run(hipStream_t s) {
 }
 }  // namespace
 
+void *operator new(size_t n) {
+    void *p = no_memory && !inside ? nullptr : std::malloc(std::max<size_t>(n, 1));
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 extern "C" {
 // what the tests read and set
 long fake_calls(const char *name) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     return calls[name];
 }
 void fake_reset() {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     calls.clear();
     on_wrong = false;
     peak = held;
@@ -91,12 +108,13 @@ size_t fake_held() { return held; }
 size_t fake_peak() { return peak; }
 void fake_limit(size_t bytes) { limit = bytes; }
 void fake_fail_copy(long after) { fail_copy = after; }
+void fake_no_memory(int on) { no_memory = on != 0; }   // host allocations (operator new) fail
 void fake_expect_device(int d) { expected = d; }
 int fake_on_wrong_device() { return on_wrong; }
 void fake_set_current(int d) { current = d; }
 size_t fake_bytes_to_pageable() { return copied_to_pageable; }
 size_t fake_pending() {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     size_t n = 0;
     for (auto &q : queued) n += q.second.size();
     return n;
@@ -117,7 +135,7 @@ hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return get(p, n, false,
 hipError_t hipFree(void *p) { return drop(p, "hipFree"); }
 hipError_t hipHostFree(void *p) { return drop(p, "hipHostFree"); }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     std::memset(a, 0, sizeof(*a));
     const Mem *m = find(p);
     a->type = m ? (m->device ? hipMemoryTypeDevice : hipMemoryTypeHost) : hipMemoryTypeUnregistered;
@@ -130,13 +148,13 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
 }
 hipError_t hipStreamDestroy(hipStream_t s) { std::free((void *)s); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     note("hipStreamSynchronize");
     run(s);
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     note("hipMemcpyAsync");
     if (fail_copy == 0) return hipErrorInvalidValue;
     if (fail_copy > 0) --fail_copy;
@@ -146,7 +164,7 @@ hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, h
 }
 hipError_t hipMemcpy2DAsync(void *dst, size_t dp, const void *src, size_t sp, size_t w, size_t h, hipMemcpyKind,
                             hipStream_t s) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     for (size_t y = 0; y < h; ++y) queued[s].push_back(Copy{(char *)dst + y * dp, (const char *)src + y * sp, w});
     return hipSuccess;
 }
@@ -156,7 +174,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCre
 hipError_t hipEventDestroy(hipEvent_t e) { std::free((void *)e); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { *(hipStream_t *)e = s; return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t e) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     run(*(hipStream_t *)e);
     return hipSuccess;
 }
@@ -164,7 +182,7 @@ hipError_t hipEventQuery(hipEvent_t e) { return hipEventSynchronize(e); }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {
-    std::lock_guard<std::mutex> lk(mu);
+    Lock lk;
     note("hipLaunchKernel", true);
     return hipSuccess;
 }

@@ -141,3 +141,34 @@ for kind in (fm.MEM_HOST, fm.MEM_DEVICE):
         assert st == fm.EDEVICE and pending == 0, (st, pending)
     s.close()
 """)
+
+
+def test_copies_need_no_host_memory(child):
+    """A transfer while the process has no memory left (operator new throws):
+    the calls still copy, no exception leaves them."""
+    child("""
+import scenegen
+n = 5 * MB + 3
+a = np.random.default_rng(1).integers(0, 256, n, dtype=np.uint8)
+out = np.zeros(n, np.uint8)
+with fm.Handle(fm.default_config()) as h:
+    d = h.upload(a)
+    fake.fake_no_memory(1)
+    st = L.fassmvs_memcpy(h.h, out.ctypes.data, d.ptr, n, 1)
+    fake.fake_no_memory(0)
+    assert st == fm.OK and np.array_equal(out, a)
+for big in (1, 4):
+    wl = scenegen.make_workload("config1")
+    for im in (wl["ref"], *wl["views"]):
+        im["img"] = np.tile(im["img"], (big, big))
+    h, w = wl["ref"]["img"].shape
+    for kind in (fm.MEM_HOST, fm.MEM_DEVICE):
+        with fm.Handle(fm.config_from_params(wl["params"])) as hd:
+            t = hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], wl["families"])
+            held = [hd.empty((h * w * c,), np.float32) if kind else np.empty((h, w, c), np.float32) for c in (1, 3, 1)]
+            maps = [m.ptr if kind else m.ctypes.data for m in held]
+            fake.fake_no_memory(1)
+            st = L.fassmvs_poll(hd.h, t, *maps, kind, -1)
+            fake.fake_no_memory(0)
+            assert st == fm.OK
+""")
