@@ -87,30 +87,26 @@ public:
     // Ranges whose destination the runtime knows go straight there in one
     // copy.
     hipError_t to_host(const DeviceRanges &ranges, hipStream_t stream) {
-        size_t total = 0;
-        for (size_t i = 0; i < ranges.n; ++i) total += ranges.r[i].bytes;
-        if (total == 0) return hipSuccess;
-        DeviceRanges staged;
-        bool direct[3] = {true, true, true};
-        if (total >= kShare) {
-            total = 0;
-            for (size_t i = 0; i < ranges.n; ++i) {
-                const DeviceRange &r = ranges.r[i];
-                if (!pageable(r.dst)) continue;
-                direct[i] = false;
-                staged.add(r.dst, r.src, r.bytes);
-                total += r.bytes;
-            }
-        }
-        const bool slotted = total >= kShare && staged.n > 0 && slots();
+        if (ranges.n == 0) return hipSuccess;
+        DeviceRanges staged, direct;
+        const bool slotted = split(ranges, staged, direct) && slots();
+        const DeviceRanges &whole = slotted ? direct : ranges;
         hipError_t e = hipSuccess;
-        for (size_t i = 0; i < ranges.n && e == hipSuccess; ++i) {
-            const DeviceRange &r = ranges.r[i];
-            if (direct[i] || !slotted) e = hipMemcpyAsync(r.dst, r.src, r.bytes, hipMemcpyDeviceToHost, stream);
-        }
+        for (size_t i = 0; i < whole.n && e == hipSuccess; ++i)
+            e = hipMemcpyAsync(whole.r[i].dst, whole.r[i].src, whole.r[i].bytes, hipMemcpyDeviceToHost, stream);
         if (e == hipSuccess && slotted) e = through_slots(staged, stream);
         const hipError_t es = hipStreamSynchronize(stream);
         return e == hipSuccess ? es : e;
+    }
+
+    // What the first to_host of these ranges (of so many bytes) would make,
+    // slots and helpers, ahead of it: while a frame runs.
+    void prepare(const DeviceRanges &ranges) {
+        DeviceRanges staged, direct;
+        if (!pin_ && split(ranges, staged, direct)) prepare(kShare);
+    }
+    void prepare(size_t bytes) {
+        if (!pin_ && bytes >= kShare && slots()) helpers();
     }
 
     static constexpr size_t kPiece = 128 << 10;
@@ -130,6 +126,22 @@ private:
         if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeUnregistered;
         (void)hipGetLastError();
         return true;
+    }
+
+    // The ranges into ordinary memory and the others; whether the first are
+    // worth the slots.
+    static bool split(const DeviceRanges &ranges, DeviceRanges &staged, DeviceRanges &direct) {
+        size_t total = 0;
+        for (size_t i = 0; i < ranges.n; ++i) total += ranges.r[i].bytes;
+        if (total < kShare) return false;
+        total = 0;
+        for (size_t i = 0; i < ranges.n; ++i) {
+            const DeviceRange &r = ranges.r[i];
+            const bool own = pageable(r.dst);
+            (own ? staged : direct).add(r.dst, r.src, r.bytes);
+            total += own ? r.bytes : 0;
+        }
+        return total >= kShare;
     }
 
     // (after an error copies into the slots may still run)
@@ -183,15 +195,19 @@ private:
         return true;
     }
 
+    void helpers() {
+        const int want = std::min(kHelpers, (int)std::thread::hardware_concurrency() / 2);
+        try {
+            while ((int)threads_.size() < want) threads_.emplace_back([this] { help(); });
+        } catch (...) {   // no thread, or no memory for one: with fewer
+        }
+    }
+
     // Helpers take part between a session's start and its end.
     struct Session {
         HostMover &m;
         explicit Session(HostMover &mm) : m(mm) {
-            const int want = std::min(kHelpers, (int)std::thread::hardware_concurrency() / 2);
-            try {
-                while ((int)m.threads_.size() < want) m.threads_.emplace_back([&mm] { mm.help(); });
-            } catch (...) {   // no thread, or no memory for one: with fewer
-            }
+            m.helpers();
             {
                 std::lock_guard<std::mutex> lk(m.m_);
                 m.active_.store(true);

@@ -1351,15 +1351,19 @@ fassmvs_status enqueue_frame_graph(fassmvs_handle *h, const FramePlan &P) {
     return FASSMVS_OK;
 }
 
-// A finished frame's level-0 maps of N pixels (held by `from`) to the
-// caller's buffers (NULL: not wanted), complete when this returns.
-fassmvs_status copy_maps(fassmvs_handle *h, fassmvs_handle *from, size_t N, float *depth, float *normal, float *conf,
-                         int mem_kind) {
+// A frame's level-0 maps of N pixels (held by `from`) and the caller's
+// buffers for them (NULL: not wanted).
+DeviceRanges frame_maps(const fassmvs_handle *from, size_t N, float *depth, float *normal, float *conf) {
     const auto &B = from->lb[0];
     DeviceRanges maps;
     maps.add(depth, B.depth.p, N * 4);
     maps.add(normal, B.normal.p, N * 12);
     maps.add(conf, B.conf.p, N * 4);
+    return maps;
+}
+
+// The finished frame's maps to the caller, complete when this returns.
+fassmvs_status copy_maps(fassmvs_handle *h, const DeviceRanges &maps, int mem_kind) {
     if (mem_kind == FASSMVS_MEM_HOST) {
         HIPCHK(h, h->mover.to_host(maps, h->stream), "output copy");
     } else {
@@ -2117,7 +2121,10 @@ fassmvs_status fassmvs_poll_batch(fassmvs_handle *h, uint64_t ticket, int32_t in
     if (index < 0 || index >= h->batch_n) return fail(h, FASSMVS_EINVAL, "frame index outside the batch");
     if (mem_kind != FASSMVS_MEM_HOST && mem_kind != FASSMVS_MEM_DEVICE) return fail(h, FASSMVS_EINVAL, "bad mem_kind");
     HIPCHK(h, hipSetDevice(h->cfg.device), "hipSetDevice");
+    const fassmvs_handle *ch = h->children[index];
+    const DeviceRanges maps = frame_maps(ch, (size_t)ch->plan.w * ch->plan.h, depth, normal, confidence);
     if (h->batch_busy) {
+        if (mem_kind == FASSMVS_MEM_HOST) h->mover.prepare(maps);
         auto t0 = std::chrono::steady_clock::now();
         for (;;) {
             hipError_t e = hipEventQuery(h->done);
@@ -2134,8 +2141,7 @@ fassmvs_status fassmvs_poll_batch(fassmvs_handle *h, uint64_t ticket, int32_t in
         }
         h->batch_busy = false;
     }
-    fassmvs_handle *ch = h->children[index];
-    return copy_maps(h, ch, (size_t)ch->plan.w * ch->plan.h, depth, normal, confidence, mem_kind);
+    return copy_maps(h, maps, mem_kind);
 }
 
 fassmvs_status fassmvs_batch_tuning(fassmvs_handle *h, int32_t *rows_per_thread, int32_t *sweep_blocks,
@@ -2265,6 +2271,8 @@ fassmvs_status fassmvs_poll(fassmvs_handle *h, uint64_t ticket, float *depth, fl
     if (!h->busy || ticket != h->ticket) return fail(h, FASSMVS_ENOTFOUND, "unknown ticket");
     if (mem_kind != FASSMVS_MEM_HOST && mem_kind != FASSMVS_MEM_DEVICE) return fail(h, FASSMVS_EINVAL, "bad mem_kind");
     HIPCHK(h, hipSetDevice(h->cfg.device), "hipSetDevice");
+    const DeviceRanges maps = frame_maps(h, (size_t)h->out_w * h->out_h, depth, normal, confidence);
+    if (mem_kind == FASSMVS_MEM_HOST) h->mover.prepare(maps);
     auto t0 = std::chrono::steady_clock::now();
     for (;;) {
         hipError_t e = hipEventQuery(h->done);
@@ -2281,8 +2289,7 @@ fassmvs_status fassmvs_poll(fassmvs_handle *h, uint64_t ticket, float *depth, fl
     }
     {
         Timer t(h, ST_OUTPUT);
-        const fassmvs_status st =
-            copy_maps(h, h, (size_t)h->out_w * h->out_h, depth, normal, confidence, mem_kind);
+        const fassmvs_status st = copy_maps(h, maps, mem_kind);
         if (st != FASSMVS_OK) return st;
     }
     // the maps are there; the timers' last event may not be

@@ -577,6 +577,9 @@ fassmvs_status fassmvs_server_submit(fassmvs_server *s, int32_t stream_id, const
         s->queue.push_back(std::move(req));
     }
     s->cv_work.notify_all();
+    // what the first fetch needs, while the frame runs
+    std::unique_lock<std::mutex> flk(s->fetch_mu, std::try_to_lock);
+    if (flk.owns_lock() && hipSetDevice(s->cfg.device) == hipSuccess) s->mover.prepare(N * 20);
     return FASSMVS_OK;
 }
 

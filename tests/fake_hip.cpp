@@ -42,6 +42,7 @@ std::map<std::string, long> calls;
 thread_local int current = 0;
 size_t held = 0, peak = 0, limit = SIZE_MAX, copied_to_pageable = 0;
 long fail_copy = -1;      // this many more copies succeed
+std::atomic<long> not_ready{0};   // this many event queries say so
 bool on_wrong = false;    // a call for another device than `expected`
 int expected = -1;
 char symbol[64 << 20];    // device variables
@@ -108,6 +109,7 @@ size_t fake_held() { return held; }
 size_t fake_peak() { return peak; }
 void fake_limit(size_t bytes) { limit = bytes; }
 void fake_fail_copy(long after) { fail_copy = after; }
+void fake_not_ready(long n) { not_ready = n; }
 void fake_no_memory(int on) { no_memory = on != 0; }   // host allocations (operator new) fail
 void fake_expect_device(int d) { expected = d; }
 int fake_on_wrong_device() { return on_wrong; }
@@ -178,7 +180,13 @@ hipError_t hipEventSynchronize(hipEvent_t e) {
     run(*(hipStream_t *)e);
     return hipSuccess;
 }
-hipError_t hipEventQuery(hipEvent_t e) { return hipEventSynchronize(e); }
+hipError_t hipEventQuery(hipEvent_t e) {
+    if (not_ready > 0) {
+        --not_ready;
+        return hipErrorNotReady;
+    }
+    return hipEventSynchronize(e);
+}
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {

@@ -172,3 +172,50 @@ for big in (1, 4):
             fake.fake_no_memory(0)
             assert st == fm.OK
 """)
+
+
+def test_first_poll_finds_the_slots_ready(child):
+    """The pinned slots and the helper threads are made while the frame runs: a
+    poll that finds the frame finished after one that did not (a fetch)
+    allocates nothing and starts no thread."""
+    child("""
+import os, scenegen
+threads = lambda: len(os.listdir("/proc/self/task"))
+wl = scenegen.make_workload("config1")
+for im in (wl["ref"], *wl["views"]):
+    im["img"] = np.tile(im["img"], (4, 4))
+h, w = wl["ref"]["img"].shape
+maps = [np.empty((h, w, c), np.float32) for c in (1, 3, 1)]
+ptrs = [m.ctypes.data for m in maps]
+
+def quiet(call):
+    fake.fake_reset()
+    n = threads()
+    assert call() == fm.OK
+    assert fake.fake_calls(b"hipHostMalloc") == 0 and threads() == n
+
+with fm.Handle(fm.config_from_params(wl["params"])) as hd:
+    t = hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], wl["families"])
+    fake.fake_not_ready(1)
+    assert L.fassmvs_poll(hd.h, t, *ptrs, fm.MEM_HOST, 0) == fm.PENDING
+    quiet(lambda: L.fassmvs_poll(hd.h, t, *ptrs, fm.MEM_HOST, -1))
+with fm.Handle(fm.config_from_params(wl["params"])) as hd:
+    t = hd.submit_batch([wl, wl])
+    fake.fake_not_ready(1)
+    assert L.fassmvs_poll_batch(hd.h, t, 0, *ptrs, fm.MEM_HOST, 0) == fm.PENDING
+    quiet(lambda: L.fassmvs_poll_batch(hd.h, t, 0, *ptrs, fm.MEM_HOST, -1))
+s = fm.Server(fm.config_from_params(wl["params"]), n_slots=1)
+sid = s.open_stream(wl["K"], w, h, wl["families"], max_keyframes=2, min_baseline=0.0)
+for v in (*wl["views"], wl["ref"]):
+    s.submit(sid, v["img"], v["R"], v["t"])
+    r = s.next()
+assert r["status"] == fm.OK, r
+quiet(lambda: L.fassmvs_server_fetch(s.s, r["request_id"], *ptrs, fm.MEM_HOST))
+s.close()
+# small frames: none
+wl = scenegen.make_workload("config1")
+with fm.Handle(fm.config_from_params(wl["params"])) as hd:
+    n = threads()
+    hd.run_frame(wl)
+    assert threads() == n
+""")
