@@ -2454,10 +2454,13 @@ fassmvs_status fassmvs_level_map(fassmvs_handle *h, int32_t level, int32_t what,
                 bytes = N * L.D * 2;
                 if (L.narrow && h->S.bytes >= N * L.D && h->sgmbuf[what - 10].bytes >= bytes) {
                     if (dst_bytes < bytes) return fail(h, FASSMVS_EINVAL, "destination too small");
-                    // straight into a device buffer, else through one
+                    HIPCHK(h, hipSetDevice(h->cfg.device), "hipSetDevice");
+                    // straight into a buffer of this device, else through one
                     hipPointerAttribute_t at;
-                    const bool direct = hipPointerGetAttributes(&at, dst) == hipSuccess && at.type == hipMemoryTypeDevice;
-                    if (!direct) (void)hipGetLastError();
+                    const bool known = hipPointerGetAttributes(&at, dst) == hipSuccess;
+                    if (!known) (void)hipGetLastError();
+                    const bool direct = known && at.type == hipMemoryTypeDevice && at.device == h->cfg.device &&
+                                        (uintptr_t)dst % 2 == 0;
                     void *wide = dst;
                     if (!direct) HIPCHK(h, hipMalloc(&wide, bytes), "level map copy");
                     hipError_t e = launch_widen((const uint8_t *)h->S.p, src, L.w, L.h, L.D, (uint16_t *)wide, h->stream);

@@ -219,3 +219,46 @@ with fm.Handle(fm.config_from_params(wl["params"])) as hd:
     hd.run_frame(wl)
     assert threads() == n
 """)
+
+
+NARROW = """
+import scenegen
+wl = scenegen.make_workload("config1")
+for im in (wl["ref"], *wl["views"]):
+    im["img"] = np.tile(im["img"], (9, 7))[:1024, :1088]
+h, w = wl["ref"]["img"].shape
+wl["families"][0]["count"] = D = 128
+wl["params"].update(n_levels=1, n_paths=4, p1=50, p2_mode=1)
+size = h * w * D * 2
+
+def frame(device):
+    hd = fm.Handle(fm.config_from_params(wl["params"], keep_levels=1, device=device))
+    t = hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], wl["families"])
+    assert L.fassmvs_poll(hd.h, t, None, None, None, fm.MEM_HOST, -1) == fm.OK
+    fake.fake_reset()
+    return hd
+"""
+
+
+def test_path_costs_on_the_handles_device(child):
+    """level_map widens 9-bit path costs on the handle's device, whatever the
+    calling thread's is, and writes to another device's memory by a copy."""
+    child(NARROW + """
+hd = frame(1)
+fake.fake_expect_device(1)
+for at in (1, 0):
+    fake.fake_set_current(at)
+    with_dst = C.c_void_p()
+    assert L.fassmvs_device_alloc(hd.h, size, C.byref(with_dst)) == fm.OK
+    fake.fake_reset()
+    fake.fake_set_current(0)
+    assert L.fassmvs_level_map(hd.h, 0, 10, with_dst, size) == fm.OK
+    assert fake.fake_calls(b"hipLaunchKernel") >= 1 and not fake.fake_on_wrong_device()
+    assert fake.fake_calls(b"hipMemcpyAsync") == 0
+fake.fake_expect_device(-1)
+other = fm.Handle(fm.default_config(device=0))
+there = other.empty((size,), np.uint8)
+fake.fake_reset()
+assert L.fassmvs_level_map(hd.h, 0, 10, there.ptr, size) == fm.OK
+assert fake.fake_calls(b"hipMemcpyAsync") >= 1
+""")
