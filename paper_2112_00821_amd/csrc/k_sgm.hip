@@ -283,25 +283,27 @@ static void launch_wta(const SgmArgs &a, hipStream_t s) {
 #undef FMVS_WTA
 }
 
-// One thread per label pair.
+// One thread per label pair of the n pixels from pixel p0 on.
 __global__ __launch_bounds__(256) void k_widen(const uint8_t *__restrict__ S, const uint8_t *__restrict__ in, size_t N,
-                                               int D, uint16_t *__restrict__ dst) {
+                                               int D, size_t p0, size_t n, uint16_t *__restrict__ dst) {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const size_t p = i / (unsigned)(D / 2);
-    if (p >= N) return;
-    const int pair = (int)(i - p * (unsigned)(D / 2));
+    const size_t q = i / (unsigned)(D / 2);
+    if (q >= n) return;
+    const size_t p = p0 + q;
+    const int pair = (int)(i - q * (unsigned)(D / 2));
     const uint32_t *m = (const uint32_t *)(in + narrow_bits_at(N, D)) +
                         (p * ((D + 127) / 128) + (pair >> 6)) * 4 + 2 * ((pair >> 5) & 1);
     for (int o = 0; o < 2; ++o) {
         const size_t at = p * D + 2 * pair + o;
-        dst[at] = (uint16_t)(S[at] + in[at] + (((m[o] >> (pair & 31)) & 1u) << 8));
+        dst[q * D + 2 * pair + o] = (uint16_t)(S[at] + in[at] + (((m[o] >> (pair & 31)) & 1u) << 8));
     }
 }
 
-hipError_t launch_widen(const uint8_t *S, const void *narrow, int w, int h, int D, uint16_t *dst, hipStream_t s) {
-    const size_t N = (size_t)w * h, n = N * (D / 2);
-    hipLaunchKernelGGL(k_widen, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, S, (const uint8_t *)narrow, N, D,
-                       dst);
+hipError_t launch_widen(const uint8_t *S, const void *narrow, size_t N, int D, size_t p0, size_t n, uint16_t *dst,
+                        hipStream_t s) {
+    const size_t pairs = n * (D / 2);
+    hipLaunchKernelGGL(k_widen, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, s, S, (const uint8_t *)narrow, N,
+                       D, p0, n, dst);
     return hipGetLastError();
 }
 

@@ -87,8 +87,10 @@ int sgm_paths(int dir, int w, int h);
 // Whether the path costs of these arguments (shape, families, penalties, path
 // gradient) are held narrow in a frame of its own.
 bool sgm_narrow(const SgmArgs &a);
-// Narrow path costs of one direction as 16-bit ones: dst[h][w][D].
-hipError_t launch_widen(const uint8_t *S, const void *narrow, int w, int h, int D, uint16_t *dst, hipStream_t s);
+// Narrow path costs of one direction of N pixels as 16-bit ones, the n pixels
+// from pixel p0 on: dst[n][D].
+hipError_t launch_widen(const uint8_t *S, const void *narrow, size_t N, int D, size_t p0, size_t n, uint16_t *dst,
+                        hipStream_t s);
 hipError_t launch_sgm(const SgmArgs &a, hipStream_t s);
 // several frames' aggregation in one persistent launch (see k_sgm.hip)
 size_t sgm_batch_bytes(int n);

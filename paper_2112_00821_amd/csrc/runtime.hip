@@ -2455,20 +2455,27 @@ fassmvs_status fassmvs_level_map(fassmvs_handle *h, int32_t level, int32_t what,
                 if (L.narrow && h->S.bytes >= N * L.D && h->sgmbuf[what - 10].bytes >= bytes) {
                     if (dst_bytes < bytes) return fail(h, FASSMVS_EINVAL, "destination too small");
                     HIPCHK(h, hipSetDevice(h->cfg.device), "hipSetDevice");
-                    // straight into a buffer of this device, else through one
+                    // straight into a buffer of this device, else part by part
+                    // through one of the frame's own
                     hipPointerAttribute_t at;
                     const bool known = hipPointerGetAttributes(&at, dst) == hipSuccess;
                     if (!known) (void)hipGetLastError();
                     const bool direct = known && at.type == hipMemoryTypeDevice && at.device == h->cfg.device &&
                                         (uintptr_t)dst % 2 == 0;
-                    void *wide = dst;
-                    if (!direct) HIPCHK(h, hipMalloc(&wide, bytes), "level map copy");
-                    hipError_t e = launch_widen((const uint8_t *)h->S.p, src, L.w, L.h, L.D, (uint16_t *)wide, h->stream);
-                    if (e == hipSuccess && !direct)
-                        e = hipMemcpyAsync(dst, wide, bytes, hipMemcpyDeviceToDevice, h->stream);
-                    const hipError_t e2 = hipStreamSynchronize(h->stream);
-                    if (!direct) hipFree(wide);
-                    HIPCHK(h, e == hipSuccess ? e2 : e, "level map copy");
+                    // (the winner's aggregates: 6 bytes a pixel, not read again)
+                    const size_t part = direct ? N : h->c3.bytes / (2 * L.D);
+                    if (part == 0) return fail(h, FASSMVS_EDEVICE, "level map copy");
+                    hipError_t e = hipSuccess;
+                    for (size_t p = 0; p < N && e == hipSuccess; p += part) {
+                        const size_t n = std::min(part, N - p);
+                        uint16_t *to = direct ? (uint16_t *)dst : (uint16_t *)h->c3.p;
+                        e = launch_widen((const uint8_t *)h->S.p, src, N, L.D, p, n, to, h->stream);
+                        if (e == hipSuccess && !direct)
+                            e = hipMemcpyAsync((uint8_t *)dst + p * L.D * 2, to, n * L.D * 2, hipMemcpyDeviceToDevice,
+                                               h->stream);
+                    }
+                    const hipError_t es = hipStreamSynchronize(h->stream);
+                    HIPCHK(h, e == hipSuccess ? es : e, "level map copy");
                     return FASSMVS_OK;
                 }
                 break;

@@ -69,3 +69,20 @@ def test_narrow_equals_wide(planes, families, levels, window, paths, variant):
             maps.append(m)
     for a, b in zip(*maps):
         assert np.array_equal(a, b)
+
+
+def test_path_costs_at_any_address():
+    """level_map of 9-bit path costs to an odd address (part by part through
+    the handle's own memory) gives what it gives to an even one."""
+    import paper_2112_00821_amd as fm
+    wl, D = _frame(136, 2, 1, 0, 4, 0)
+    with fm.Handle(fm.config_from_params(wl["params"], keep_levels=1)) as hd:
+        hd.run_frame(wl)
+        w, h = hd.level_size(0)
+        n = h * w * D * 2
+        for r in range(4):
+            dst = hd.empty((n + 2,), np.uint8).fill(0xA5)
+            assert fm.lib().fassmvs_level_map(hd.h, 0, 10 + r, dst.ptr + 1, n) == fm.OK
+            got = dst.numpy()
+            assert got[0] == got[-1] == 0xA5
+            assert np.array_equal(got[1:-1].view(np.uint16).reshape(h, w, D), hd.level_map(0, 10 + r, D=D))

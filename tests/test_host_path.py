@@ -262,3 +262,20 @@ fake.fake_reset()
 assert L.fassmvs_level_map(hd.h, 0, 10, there.ptr, size) == fm.OK
 assert fake.fake_calls(b"hipMemcpyAsync") >= 1
 """)
+
+
+def test_path_costs_need_no_memory(child):
+    """level_map of 9-bit path costs with no device memory left, into device
+    and into other memory."""
+    child(NARROW + """
+hd = frame(0)
+there = hd.empty((size,), np.uint8)
+host = np.empty(size, np.uint8)
+fake.fake_reset()
+fake.fake_limit(fake.fake_held())
+for dst in (there.ptr, host.ctypes.data, fake.fake_pinned(size)):
+    before = fake.fake_held()
+    assert L.fassmvs_level_map(hd.h, 0, 10, dst, size) == fm.OK, L.fassmvs_last_error(hd.h)
+    assert fake.fake_peak() == before == fake.fake_held() and fake.fake_pending() == 0
+assert L.fassmvs_level_map(hd.h, 0, 10, there.ptr, size - 1) == fm.EINVAL
+""")
