@@ -167,6 +167,7 @@ struct fassmvs_handle {
     DevBuf pyr[kMaxViews + 1];       // every level of each image, level 0 first
     DevBuf ct, S, wta, c3, params, work_ctr;
     DevBuf sgmbuf[8];
+    bool sgmbuf_narrow = false;   // they hold a frame's level-0 path costs, narrow
     DevBuf sbar;
     DevBuf post_tmp, post_m0, post_m1, post_hits;
     struct LevelBufs {
@@ -1707,6 +1708,7 @@ fassmvs_status submit_frame_locked(fassmvs_handle *h, const fassmvs_image *ref, 
     h->cur_level = -1;
     if ((st = upload_frame(h, h->mover, P, ref, views, mem_kind)) != FASSMVS_OK) return st;
     if ((st = enqueue_frame_graph(h, P)) != FASSMVS_OK) return st;
+    h->sgmbuf_narrow = P.lv[0].narrow;
     HIPCHK(h, hipMemcpyAsync(h->work_host, h->work_ctr.p, 8, hipMemcpyDeviceToHost, h->stream), "work counter");
     HIPCHK(h, hipEventRecord(h->done, h->stream), "event record");
     h->out_w = P.w;
@@ -2452,7 +2454,7 @@ fassmvs_status fassmvs_level_map(fassmvs_handle *h, int32_t level, int32_t what,
                 // path costs of direction r (each direction has its own buffer)
                 src = h->sgmbuf[what - 10].p;
                 bytes = N * L.D * 2;
-                if (L.narrow && h->S.bytes >= N * L.D && h->sgmbuf[what - 10].bytes >= bytes) {
+                if (h->sgmbuf_narrow && h->S.bytes >= N * L.D && h->sgmbuf[what - 10].bytes >= bytes) {
                     if (dst_bytes < bytes) return fail(h, FASSMVS_EINVAL, "destination too small");
                     HIPCHK(h, hipSetDevice(h->cfg.device), "hipSetDevice");
                     // straight into a buffer of this device, else part by part
@@ -2811,6 +2813,7 @@ fassmvs_status fassmvs_stage_sgm(fassmvs_handle *h, int32_t w, int32_t hgt, int3
     if (Lr) {
         for (int d = 0; d < n_paths; ++d) bufs[d] = Lr + (size_t)d * ND;
     } else {
+        h->sgmbuf_narrow = false;
         for (int d = 0; d < n_paths; ++d) {
             if ((st = ensure(h, h->sgmbuf[d], ND * 2)) != FASSMVS_OK) return st;
             bufs[d] = (uint16_t *)h->sgmbuf[d].p;
@@ -2864,6 +2867,7 @@ fassmvs_status fassmvs_stage_sgm_pg(fassmvs_handle *h, int32_t w, int32_t hgt, i
     if (Lr) {
         for (int d = 0; d < n_paths; ++d) bufs[d] = Lr + (size_t)d * ND;
     } else {
+        h->sgmbuf_narrow = false;
         for (int d = 0; d < n_paths; ++d) {
             if ((st = ensure(h, h->sgmbuf[d], ND * 2)) != FASSMVS_OK) return st;
             bufs[d] = (uint16_t *)h->sgmbuf[d].p;

@@ -279,3 +279,31 @@ for dst in (there.ptr, host.ctypes.data, fake.fake_pinned(size)):
     assert fake.fake_peak() == before == fake.fake_held() and fake.fake_pending() == 0
 assert L.fassmvs_level_map(hd.h, 0, 10, there.ptr, size - 1) == fm.EINVAL
 """)
+
+
+def test_path_costs_after_a_stage_call(child):
+    """An aggregation stage call without an output for its path costs leaves
+    them in the handle's buffers, as 16 bits: level_map hands those out as
+    they are, also after a frame that held its own as 9 bits."""
+    child(NARROW + """
+hd = frame(0)
+there = hd.empty((size,), np.uint8)
+S, ref = hd.empty((h, w, D), np.uint8), hd.empty((h, w), np.uint8)
+lut = np.full(256, 400, np.int32)
+wta, c3 = hd.empty((h, w), np.uint16), hd.empty((h, w, 3), np.uint16)
+for call in ("plain", "pg"):
+    hd = frame(0)
+    W = np.array([D], np.int32)
+    if call == "plain":
+        st = L.fassmvs_stage_sgm(hd.h, w, h, 1, W.ctypes.data, S.vp, None, None, ref.vp, 50, lut.ctypes.data, 4, None,
+                                 None, wta.vp, c3.vp)
+    else:
+        delta, n, K, step = np.linspace(1.0, 2.0, D), np.array([0, 0, -1.0]), np.eye(3), np.ones(1)
+        st = L.fassmvs_stage_sgm_pg(hd.h, w, h, 1, W.ctypes.data, W.ctypes.data, S.vp, None, ref.vp, 50,
+                                    lut.ctypes.data, 4, delta.ctypes.data, n.ctypes.data, K.ctypes.data,
+                                    step.ctypes.data, None, None, wta.vp, c3.vp)
+    assert st == fm.OK
+    fake.fake_reset()
+    assert L.fassmvs_level_map(hd.h, 0, 10, there.ptr, size) == fm.OK
+    assert fake.fake_calls(b"hipLaunchKernel") == 0 and fake.fake_calls(b"hipMemcpyAsync") == 1
+""")
