@@ -2454,7 +2454,7 @@ fassmvs_status fassmvs_level_map(fassmvs_handle *h, int32_t level, int32_t what,
                 // path costs of direction r (each direction has its own buffer)
                 src = h->sgmbuf[what - 10].p;
                 bytes = N * L.D * 2;
-                if (h->sgmbuf_narrow && h->S.bytes >= N * L.D && h->sgmbuf[what - 10].bytes >= bytes) {
+                if (L.narrow && h->sgmbuf_narrow && h->S.bytes >= N * L.D && h->sgmbuf[what - 10].bytes >= bytes) {
                     if (dst_bytes < bytes) return fail(h, FASSMVS_EINVAL, "destination too small");
                     HIPCHK(h, hipSetDevice(h->cfg.device), "hipSetDevice");
                     // straight into a buffer of this device, else part by part
