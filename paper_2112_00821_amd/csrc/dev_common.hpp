@@ -61,19 +61,20 @@ __device__ __forceinline__ float warp_sample(const uint8_t *__restrict__ src, in
 
 // The same sample from a packed view (launch_pack_quads: texel (x, y) and its
 // right, lower and lower-right neighbours, border replicated, in one 32-bit
-// word), split into the word's byte offset with the bilinear fractions and
-// the interpolation, so a kernel can have many of the loads in flight.
+// word), split into the texel with the bilinear fractions, the word's byte
+// offset and the interpolation, so a kernel can have many of the loads in
+// flight.
 // (hx, hy, hz): the homography applied to the sample point.
 // INSIDE: the reference region maps in front of the view and inside
 // [0, sw - 1] x [0, sh - 1] (warp_region_inside): there the reciprocal guard
 // and the border clamps change nothing, so the same operations without them
 // give the same value.
-struct QuadSample {
-    uint32_t offset;
+struct Sample {
+    uint32_t x, y;   // upper left texel
     float ax, ay;
 };
 template <bool INSIDE>
-__device__ __forceinline__ QuadSample warp_quad(int sw, int sh, double hx, double hy, double hz) {
+__device__ __forceinline__ Sample warp_point(int sw, int sh, double hx, double hy, double hz) {
     const double r = recip(hz);
     const double inv = INSIDE || hz > 1e-300 ? r : 0.0;
     double sx = __builtin_fma(hx, inv, -0.5);
@@ -82,12 +83,15 @@ __device__ __forceinline__ QuadSample warp_quad(int sw, int sh, double hx, doubl
         sx = __builtin_fmin(__builtin_fmax(sx, 0.0), (double)(sw - 1));
         sy = __builtin_fmin(__builtin_fmax(sy, 0.0), (double)(sh - 1));
     }
-    const uint32_t xa = (uint32_t)(int)sx, ya = (uint32_t)(int)sy;
-    QuadSample q;
+    Sample q;
+    q.x = (uint32_t)(int)sx;
+    q.y = (uint32_t)(int)sy;
     q.ax = (float)__builtin_amdgcn_fract(sx);
     q.ay = (float)__builtin_amdgcn_fract(sy);
-    q.offset = (__umul24(ya, (uint32_t)sw) + xa) << 2;
     return q;
+}
+__device__ __forceinline__ uint32_t quad_offset(const Sample &q, int sw) {
+    return (__umul24(q.y, (uint32_t)sw) + q.x) << 2;
 }
 __device__ __forceinline__ float quad_value(uint32_t t, float ax, float ay) {
     const float i00 = (float)(t & 0xFFu), i10 = (float)((t >> 8) & 0xFFu), i01 = (float)((t >> 16) & 0xFFu),

@@ -21,7 +21,9 @@ hipError_t sweep_launch_batch_cfg(const SweepArgs *list, const int *prefix, int 
 
 // Tile height / 4 (one wavefront per 4 rows): 8 halves the halo of 4, 4 gives
 // more workgroups and smaller unions of label windows.
+// (views in bytes: built for 4 only)
 int sweep_rpt(const SweepArgs &a) {
+    if (a.views[0] && !a.warped) return 4;
     return a.rows_per_thread == 4 ? 4 : (a.rows_per_thread == 8 ? 8 : (a.cost == 1 ? 4 : 8));
 }
 

@@ -42,6 +42,12 @@
 
 namespace fmvs {
 
+// Where the samples come from: packed 2x2 texels, pre-warped views, or the
+// views' own bytes, four loads a sample.  The bytes are for views that a call
+// has no room to pack, or whose packed texels 32-bit offsets do not reach
+// (2^30 texels); 1280x720, 4 views, 64 labels, 5x5: PLACEHOLDER.
+enum SweepSource { kPacked, kWarped, kBytes };
+
 namespace {
 constexpr int TW = 64;       // tile width: a wavefront's row
 constexpr int RPT = 4;       // rows per thread
@@ -101,10 +107,11 @@ struct SweepTile {
 };
 
 // What a wavefront holds of the samples it has requested: the packed 2x2
-// texels (or the value itself, from pre-warped views) and the fractions.
-template <int NST>
+// texels (four bytes each in a register of its own; the value itself, from
+// pre-warped views) and the fractions.
+template <int NST, SweepSource SRC>
 struct Pending {
-    uint32_t tex[NST];
+    uint32_t tex[NST][SRC == kBytes ? 4 : 1];
     float ax[NST], ay[NST];
 };
 }  // namespace
@@ -150,8 +157,9 @@ __device__ __forceinline__ int xcd_logical(int b, int nb) {
 
 // One workgroup's share of the sweep of one frame: logical = tile *
 // n_chunks + chunk.
-template <int CW, int CH, int NW, bool WARPED, int COST>
+template <int CW, int CH, int NW, SweepSource SRC, int COST>
 __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
+    constexpr bool WARPED = SRC == kWarped;
     typedef SweepTile<CW, CH, NW> T;
     constexpr int NT = T::NT, RX = T::RX, RY = T::RY, RW = T::RW, RH = T::RH, NS = T::NS;
     constexpr int NST = T::NST, NFULL = T::NFULL, E = T::E, HR = T::HR;
@@ -347,6 +355,7 @@ __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
     } nx;
     double h0 = 0.0, h3 = 0.0, h6 = 0.0;
     const uint32_t *quads = nullptr;
+    const uint8_t *bytes = nullptr;
     const float *warped = nullptr;
     bool inside = false;
     int vflag = 0;   // lane i: the views' flags of the i-th plane of this window
@@ -357,7 +366,10 @@ __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
             warped = a.warped + (size_t)lab * N;
         } else {
             const FMVS_CONST_AS double *Hm = H0 + (uint32_t)__builtin_amdgcn_readfirstlane(lab * 9);
-            quads = a.quads[nx.k];
+            if (SRC == kBytes)
+                bytes = a.views[nx.k];
+            else
+                quads = a.quads[nx.k];
             inside = ((__builtin_amdgcn_readlane(vflag, nx.pos - pb) >> nx.k) & 1) != 0;
             h0 = Hm[0];
             h3 = Hm[3];
@@ -382,7 +394,7 @@ __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
         }
     };
 
-    Pending<NST> pend;
+    Pending<NST, SRC> pend;
     // Request the fetched pair's samples: coordinates, fractions and one
     // packed-texel load each.
     auto request = [&](int slot) __attribute__((always_inline)) {
@@ -391,25 +403,36 @@ __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
             for (int i = 0; i < NST; ++i) {
                 const int r = i < NFULL ? wv + i * NW : row_mix[i < NFULL ? 0 : i - NFULL];
                 const double qx = i < NFULL ? qxm : qx_mix[i < NFULL ? 0 : i - NFULL];
-                pend.tex[i] = __float_as_uint(warped[(size_t)min(max(y0 - RY + r, 0), ah - 1) * aw + (int)qx]);
+                pend.tex[i][0] = __float_as_uint(warped[(size_t)min(max(y0 - RY + r, 0), ah - 1) * aw + (int)qx]);
             }
             return;
         }
         const __amdgpu_buffer_rsrc_t rs =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(quads), 0, (int)(uint32_t)(N * 4), 0x00020000);
+            SRC == kBytes
+                ? __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(bytes), 0, (int)(uint32_t)N, 0x00020000)
+                : __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(quads), 0, (int)(uint32_t)(N * 4), 0x00020000);
         auto steps = [&](auto in) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < NST; ++i) {
                 const int r = i < NFULL ? wv + i * NW : row_mix[i < NFULL ? 0 : i - NFULL];
                 const double qx = i < NFULL ? qxm : qx_mix[i < NFULL ? 0 : i - NFULL];
-                const QuadSample q = warp_quad<decltype(in)::value>(
+                const Sample q = warp_point<decltype(in)::value>(
                     aw, ah, __builtin_fma(h0, qx, s_row[slot][0][r]), __builtin_fma(h3, qx, s_row[slot][1][r]),
                     __builtin_fma(h6, qx, s_row[slot][2][r]));
                 pend.ax[i] = q.ax;
                 pend.ay[i] = q.ay;
                 pin(pend.ax[i]);
                 pin(pend.ay[i]);
-                pend.tex[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, q.offset, 0, 0);
+                if (SRC == kBytes) {
+                    const uint32_t xb = min(q.x + 1u, (uint32_t)(aw - 1)), yb = min(q.y + 1u, (uint32_t)(ah - 1));
+                    const uint32_t ra = __umul24(q.y, (uint32_t)aw), rb = __umul24(yb, (uint32_t)aw);
+                    const uint32_t at[4] = {ra + q.x, ra + xb, rb + q.x, rb + xb};
+#pragma unroll
+                    for (int e = 0; e < (SRC == kBytes ? 4 : 1); ++e)
+                        pend.tex[i][e] = __builtin_amdgcn_raw_buffer_load_b8(rs, at[e], 0, 0);
+                } else {
+                    pend.tex[i][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, quad_offset(q, aw), 0, 0);
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -423,8 +446,9 @@ __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
     auto deliver = [&](float *buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NST; ++i) {
-            const float v =
-                WARPED ? __uint_as_float(pend.tex[i]) : quad_value(pend.tex[i], pend.ax[i], pend.ay[i]);
+            uint32_t t = pend.tex[i][0];
+            if constexpr (SRC == kBytes) t |= pend.tex[i][1] << 8 | pend.tex[i][2] << 16 | pend.tex[i][3] << 24;
+            const float v = WARPED ? __uint_as_float(t) : quad_value(t, pend.ax[i], pend.ay[i]);
             if (i < NFULL)
                 buf[(wv + i * NW) * RW + tx] = v;
             else if (word_mix[i < NFULL ? 0 : i - NFULL] >= 0)
@@ -613,11 +637,11 @@ __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
     }
 }
 
-template <int CW, int CH, int NW, bool WARPED, int COST>
-__global__ __launch_bounds__(64 * NW, kSweepWaves) void k_sweep(const SweepArgs) {
+template <int CW, int CH, int NW, SweepSource SRC, int COST>
+__global__ __launch_bounds__(64 * NW, SRC == kBytes ? 2 : kSweepWaves) void k_sweep(const SweepArgs) {
     // the arguments, in place
     ArgsC &a = *(ArgsC *)__builtin_amdgcn_kernarg_segment_ptr();
-    sweep_block<CW, CH, NW, WARPED, COST>(a, xcd_logical(blockIdx.x, gridDim.x));
+    sweep_block<CW, CH, NW, SRC, COST>(a, xcd_logical(blockIdx.x, gridDim.x));
 }
 
 // Several frames in one launch: the workgroups of frame f are the logical
@@ -630,7 +654,7 @@ __global__ __launch_bounds__(64 * NW, kSweepWaves) void k_sweep_batch(const Swee
     int f = 0;
     while (f + 1 < n && logical >= prefix[f + 1]) ++f;
     f = __builtin_amdgcn_readfirstlane(f);
-    sweep_block<CW, CH, NW, false, COST>(*(ArgsC *)(list + f), logical - prefix[f]);
+    sweep_block<CW, CH, NW, kPacked, COST>(*(ArgsC *)(list + f), logical - prefix[f]);
 }
 
 // Launch one window size and cost: tiles of 64 x 4*rpt pixels (rpt 4 or 8:
@@ -641,14 +665,16 @@ template <int CW, int CH, int COST>
 hipError_t sweep_launch_cfg(const SweepArgs &a, dim3 grid, int rpt, hipStream_t s) {
     if (rpt == 4) {
         if (a.warped)
-            hipLaunchKernelGGL((k_sweep<CW, CH, 4, true, COST>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((k_sweep<CW, CH, 4, kWarped, COST>), grid, dim3(256), 0, s, a);
+        else if (a.views[0])
+            hipLaunchKernelGGL((k_sweep<CW, CH, 4, kBytes, COST>), grid, dim3(256), 0, s, a);
         else
-            hipLaunchKernelGGL((k_sweep<CW, CH, 4, false, COST>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((k_sweep<CW, CH, 4, kPacked, COST>), grid, dim3(256), 0, s, a);
     } else {
         if (a.warped)
-            hipLaunchKernelGGL((k_sweep<CW, CH, 8, true, COST>), grid, dim3(512), 0, s, a);
+            hipLaunchKernelGGL((k_sweep<CW, CH, 8, kWarped, COST>), grid, dim3(512), 0, s, a);
         else
-            hipLaunchKernelGGL((k_sweep<CW, CH, 8, false, COST>), grid, dim3(512), 0, s, a);
+            hipLaunchKernelGGL((k_sweep<CW, CH, 8, kPacked, COST>), grid, dim3(512), 0, s, a);
     }
     return hipGetLastError();
 }

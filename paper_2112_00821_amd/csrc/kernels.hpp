@@ -29,6 +29,7 @@ struct SweepArgs {
     int cw, ch;               // census window
     int n_views, nL, nR, m;
     const uint32_t *quads[kMaxViews];   // [h][w] packed 2x2 texels of each view (launch_pack_quads)
+    const uint8_t *views[kMaxViews];    // or, where they are not packed, the views' bytes (NULL otherwise)
     int side[kMaxViews];
     int cost;                 // 0: census-Hamming, 1: NCC
     const uint64_t *ct_ref;   // [h][w] reference census (census cost)

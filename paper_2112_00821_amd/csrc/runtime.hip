@@ -2659,11 +2659,12 @@ fassmvs_status stage_cost_any(fassmvs_handle *h, int cost, int32_t w, int32_t hg
     hipError_t e = hipSuccess;
     uint32_t *quads = nullptr;   // the views' packed texels, held for this call only
     if (!warped) {
-        // (the sweep's texel offsets are 32-bit bytes of 4-byte texels)
-        if ((size_t)w * hgt >= (size_t)1 << 30) return fail(h, FASSMVS_EUNSUPPORTED, "view too large");
-        if ((e = hipMalloc((void **)&quads, (size_t)n_views * w * hgt * 4)) != hipSuccess) {
+        // (the sweep's texel offsets are 32-bit bytes of 4-byte texels); without
+        // room for them the views' own bytes are read
+        const size_t bytes = (size_t)n_views * w * hgt * 4;
+        if ((size_t)w * hgt < (size_t)1 << 30 && hipMalloc((void **)&quads, bytes) != hipSuccess) {
             (void)hipGetLastError();
-            return fail(h, FASSMVS_ENOMEM, std::string("device allocation failed: ") + hipGetErrorString(e));
+            quads = nullptr;
         }
         QuadArgs q;
         std::memset(&q, 0, sizeof(q));
@@ -2671,9 +2672,12 @@ fassmvs_status stage_cost_any(fassmvs_handle *h, int cost, int32_t w, int32_t hg
         q.h = hgt;
         for (int k = 0; k < n_views; ++k) {
             q.src[k] = views[k];
-            a.quads[k] = q.dst[k] = quads + (size_t)k * w * hgt;
+            if (quads)
+                a.quads[k] = q.dst[k] = quads + (size_t)k * w * hgt;
+            else
+                a.views[k] = views[k];
         }
-        e = launch_pack_quads(q, n_views, h->stream);
+        if (quads) e = launch_pack_quads(q, n_views, h->stream);
     }
     if (e == hipSuccess) e = launch_sweep(a, h->stream);
     if (quads) {

@@ -307,3 +307,32 @@ for call in ("plain", "pg"):
     assert L.fassmvs_level_map(hd.h, 0, 10, there.ptr, size) == fm.OK
     assert fake.fake_calls(b"hipLaunchKernel") == 0 and fake.fake_calls(b"hipMemcpyAsync") == 1
 """)
+
+
+COST = """
+def stage_cost(hd, w, h, views=2, G=8, cw=5, ncc=False):
+    ct, S = hd.empty((64,), np.uint8), hd.empty((64,), np.uint8)   # (kernels do nothing)
+    vs = (C.c_void_p * views)(*[ct.ptr] * views)
+    side = (C.c_int8 * views)(*[-1] * views)
+    g = np.array([G], np.int32)
+    H = np.tile(np.eye(3), (views, G, 1, 1))
+    f = L.fassmvs_stage_cost_ncc if ncc else L.fassmvs_stage_cost
+    return f(hd.h, w, h, ct.vp, views, vs, side, cw, cw, 1, g.ctypes.data, g.ctypes.data, H.ctypes.data, None, None, S.vp)
+"""
+
+
+@pytest.mark.parametrize("ncc", [False, True])
+def test_stage_cost_is_not_refused(child, ncc):
+    """The cost stage without device memory for its views' packed texels, and
+    for views that are too large for them."""
+    child(COST + f"ncc = {ncc}" + """
+with fm.Handle(fm.default_config()) as hd:
+    assert stage_cost(hd, 640, 480, ncc=ncc) == fm.OK
+    for w, h in ((1 << 20, 1 << 10), (32768, 32769)):
+        fake.fake_reset()
+        assert stage_cost(hd, w, h, views=1, ncc=ncc) == fm.OK, L.fassmvs_last_error(hd.h)
+        assert fake.fake_calls(b"hipLaunchKernel") == 1
+    fake.fake_limit(fake.fake_held() + 4096)
+    for w, h in ((640, 480), (1920, 1080)):
+        assert stage_cost(hd, w, h, ncc=ncc) == fm.OK, L.fassmvs_last_error(hd.h)
+""")
