@@ -170,6 +170,7 @@ struct fassmvs_handle {
     bool sgmbuf_narrow = false;   // they hold a frame's level-0 path costs, narrow
     DevBuf sbar;
     DevBuf post_tmp, post_m0, post_m1, post_hits;
+    DevBuf packed;   // the cost stage calls' packed views (packed_views)
     struct LevelBufs {
         DevBuf depth_raw, depth, nraw, normal, conf, label, fam, offs, dI, dbar, nbar;
     } lb[FASSMVS_MAX_LEVELS];
@@ -217,6 +218,40 @@ fassmvs_status dev_fail(fassmvs_handle *h, hipError_t e, const char *what) {
         if (e_ != hipSuccess) return dev_fail((h), e_, (what)); \
     } while (0)
 
+// Packed views of the cost stage calls are kept from call to call, so that a
+// call neither allocates nor frees: a free waits for the whole device, the
+// frames of other handles included (a 160x120 call beside a 2560x1472 frame:
+// 12 ms with one, 71 us without).  They are spare memory: given back when
+// the handle or its caller runs short, and never more than kMaxPacked bytes
+// (4 views of 4096x4096).  NULL where there is no room: the sweep then reads
+// the views' bytes (measured at enum SweepSource).
+constexpr size_t kMaxPacked = (size_t)256 << 20;
+
+bool give_back_packed(fassmvs_handle *h) {
+    if (!h->packed.p) return false;
+    hipFree(h->packed.p);
+    h->held -= h->packed.bytes;
+    h->packed = DevBuf();
+    return true;
+}
+
+uint32_t *packed_views(fassmvs_handle *h, size_t bytes) {
+    if (bytes > kMaxPacked) return nullptr;
+    DevBuf &b = h->packed;
+    if (b.bytes < bytes) {
+        give_back_packed(h);
+        if (h->cfg.hbm_budget_bytes && h->held + bytes > h->cfg.hbm_budget_bytes) return nullptr;
+        if (hipMalloc(&b.p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            b.p = nullptr;
+            return nullptr;
+        }
+        b.bytes = bytes;
+        h->held += bytes;
+    }
+    return (uint32_t *)b.p;
+}
+
 fassmvs_status ensure(fassmvs_handle *h, DevBuf &b, size_t bytes) {
     if (bytes == 0) bytes = 256;
     if (b.bytes >= bytes) return FASSMVS_OK;
@@ -224,7 +259,7 @@ fassmvs_status ensure(fassmvs_handle *h, DevBuf &b, size_t bytes) {
     // admission counts the exact growth)
     size_t want = h->exact_growth ? bytes : bytes + bytes / 8;
     if (h->cfg.hbm_budget_bytes && h->held - b.bytes + want > h->cfg.hbm_budget_bytes) {
-        want = bytes;
+        if (!give_back_packed(h) || h->held - b.bytes + want > h->cfg.hbm_budget_bytes) want = bytes;
         if (h->held - b.bytes + want > h->cfg.hbm_budget_bytes)
             return fail(h, FASSMVS_ENOMEM, "frame exceeds the handle's HBM budget");
     }
@@ -235,6 +270,10 @@ fassmvs_status ensure(fassmvs_handle *h, DevBuf &b, size_t bytes) {
         b.bytes = 0;
     }
     hipError_t e = hipMalloc(&b.p, want);
+    if (e != hipSuccess && give_back_packed(h)) {
+        (void)hipGetLastError();
+        e = hipMalloc(&b.p, want);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         b.p = nullptr;
@@ -2254,6 +2293,7 @@ void handle_trim(fassmvs_handle *h) {
     drop(h->post_m0);
     drop(h->post_m1);
     drop(h->post_hits);
+    drop(h->packed);
     for (auto &L : h->lb) {
         for (DevBuf *b : {&L.depth_raw, &L.depth, &L.nraw, &L.normal, &L.conf, &L.label, &L.fam, &L.offs, &L.dI,
                           &L.dbar, &L.nbar})
@@ -2327,6 +2367,7 @@ void fassmvs_destroy(fassmvs_handle *h) {
         release(h->params);
         release(h->work_ctr);
         release(h->sbar);
+        release(h->packed);
         release(h->wtab);
         for (auto &b : h->sgmbuf) release(b);
         for (auto &L : h->lb) {
@@ -2505,6 +2546,11 @@ fassmvs_status fassmvs_device_alloc(fassmvs_handle *h, size_t bytes, void **ptr)
     hipSetDevice(h->cfg.device);
     hipError_t e = hipMalloc(ptr, bytes ? bytes : 1);
     if (e != hipSuccess) {
+        std::lock_guard<std::mutex> lk(h->mu);
+        (void)hipGetLastError();
+        if (give_back_packed(h)) e = hipMalloc(ptr, bytes ? bytes : 1);
+    }
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         *ptr = nullptr;
         return fail(h, FASSMVS_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
@@ -2657,15 +2703,10 @@ fassmvs_status stage_cost_any(fassmvs_handle *h, int cost, int32_t w, int32_t hg
     a.S = S;
     a.rows_per_thread = sweep_rows();
     hipError_t e = hipSuccess;
-    uint32_t *quads = nullptr;   // the views' packed texels, held for this call only
     if (!warped) {
-        // (the sweep's texel offsets are 32-bit bytes of 4-byte texels); without
-        // room for them the views' own bytes are read
-        const size_t bytes = (size_t)n_views * w * hgt * 4;
-        if ((size_t)w * hgt < (size_t)1 << 30 && hipMalloc((void **)&quads, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            quads = nullptr;
-        }
+        // (the sweep's texel offsets are 32-bit bytes of 4-byte texels)
+        uint32_t *quads =
+            (size_t)w * hgt < (size_t)1 << 30 ? packed_views(h, (size_t)n_views * w * hgt * 4) : nullptr;
         QuadArgs q;
         std::memset(&q, 0, sizeof(q));
         q.w = w;
@@ -2680,11 +2721,7 @@ fassmvs_status stage_cost_any(fassmvs_handle *h, int cost, int32_t w, int32_t hg
         if (quads) e = launch_pack_quads(q, n_views, h->stream);
     }
     if (e == hipSuccess) e = launch_sweep(a, h->stream);
-    if (quads) {
-        const hipError_t es = hipStreamSynchronize(h->stream);
-        hipFree(quads);
-        if (e == hipSuccess) e = es;
-    }
+    if (e != hipSuccess) (void)hipStreamSynchronize(h->stream);   // the views are the caller's again
     if (e == hipErrorInvalidValue) return fail(h, FASSMVS_EUNSUPPORTED, "matching window not built");
     HIPCHK(h, e, "sweep launch");
     return FASSMVS_OK;

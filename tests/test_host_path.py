@@ -336,3 +336,44 @@ with fm.Handle(fm.default_config()) as hd:
     for w, h in ((640, 480), (1920, 1080)):
         assert stage_cost(hd, w, h, ncc=ncc) == fm.OK, L.fassmvs_last_error(hd.h)
 """)
+
+
+def test_stage_cost_keeps_its_packed_views(child):
+    """Packed views stay with the handle: a second call of the size allocates
+    and frees nothing.  They are bounded, and given back when the handle's
+    buffers, its budget or its caller's allocations run short, and with it."""
+    child(COST + """
+def quiet(*a, **kw):
+    fake.fake_reset()
+    assert stage_cost(*a, **kw) == fm.OK
+    return fake.fake_calls(b"hipMalloc") == 2 and fake.fake_calls(b"hipFree") == 2   # the test's own
+
+packed = 2 * 640 * 480 * 4
+with fm.Handle(fm.default_config()) as hd:
+    none = fake.fake_held()
+    assert stage_cost(hd, 640, 480) == fm.OK
+    params = fake.fake_held() - none - packed
+    assert 0 < params < 4096
+    assert quiet(hd, 640, 480) and quiet(hd, 320, 200) and quiet(hd, 640, 480, ncc=True)
+    assert fake.fake_held() == none + packed + params
+    assert stage_cost(hd, 8192, 8192, views=4) == fm.OK       # 1 GB packed: not kept
+    assert fake.fake_held() < none + packed + 4096
+    # the caller's allocation takes their room
+    fake.fake_limit(fake.fake_held() + 256)
+    p = C.c_void_p()
+    assert L.fassmvs_device_alloc(hd.h, packed, C.byref(p)) == fm.OK
+    assert fake.fake_held() < none + packed + 4096
+    assert stage_cost(hd, 640, 480) == fm.OK                  # (read in bytes)
+    assert L.fassmvs_device_free(hd.h, p) == fm.OK
+    assert stage_cost(hd, 640, 480) == fm.OK and quiet(hd, 640, 480)
+    # the handle's own buffers do
+    fake.fake_limit(fake.fake_held() + 256)
+    assert stage_cost(hd, 640, 480, G=200) == fm.OK, L.fassmvs_last_error(hd.h)
+    fake.fake_limit(1 << 40)
+# a budget
+n = 200 * 2 * 72
+with fm.Handle(fm.default_config(hbm_budget_bytes=n + packed)) as hd:
+    assert stage_cost(hd, 640, 480) == fm.OK and quiet(hd, 640, 480)
+    assert stage_cost(hd, 640, 480, G=200) == fm.OK, L.fassmvs_last_error(hd.h)
+assert fake.fake_held() == none, (fake.fake_held(), none)
+""")
