@@ -326,18 +326,31 @@ static bool use_packed(const SgmArgs &a) {
 // The path costs of a direction are S plus a height of at most P2, so where
 // no P2 exceeds 511 they can be held as a byte a label and a 9th bit.  The
 // two-label kernel then writes 9 bits a label and direction and the winner's
-// pass reads them, in place of 16 each; both are bound by those bytes on
-// large frames (1920x1080 x 128 labels, 3 levels, 8 paths: 1.87 -> 1.60 ms
-// and 0.88 -> 0.71 ms; 2704x1520, 4 families: 11.0 -> 9.7 and 5.7 -> 4.6 ms).
-// Below 2^27 labels the packing costs what the bytes save (1280x720 x 128,
-// 4 paths: 0.36 -> 0.39 and 0.18 -> 0.14 ms; 640x480 x 168: 0.48 -> 0.52 and
-// 0.27 -> 0.24 ms), as it does with the path gradient's arithmetic beside it
-// (1.03 -> 1.06 ms).  The winner's pass takes whole chunks of 8 labels, and
-// from 16 labels on the bits (a word of 16 bytes per 128 labels) fit behind
-// the bytes in the room of the 16-bit form.
+// pass reads them, in place of 16 each; on large frames both are bound by
+// those bytes (1920x1080 x 128 labels, 3 levels, 8 paths: 1.87 -> 1.60 ms and
+// 0.88 -> 0.71 ms; 2704x1520, 4 families: 11.0 -> 9.7 and 5.7 -> 4.6 ms).
+// What decides it is measured on one level, aggregation and winner together,
+// time of the narrow form over the wide one's:
+//  - labels missing of a pixel's last 128: a step's arithmetic is the same
+//    without them, its bytes are fewer.  8 paths, 210 million labels, mean of
+//    six processes a side (which differ by up to 1.2): 64 labels 1.15, 96 1.28,
+//    112 1.21, 120 1.02, 128 0.95; two pairs a lane 136 1.11, 168 1.05, 192
+//    1.09, 208 1.02, 216 0.92, 256 0.95; three 264 1.03, 288 1.00, 304 0.94,
+//    384 0.87; four 392 0.89, 512 0.78.
+//  - the level's size: 128 labels, 8 paths 0.99 at 109 million labels, 0.97 at
+//    150, 0.82 at 300; 4 paths 1.01 at 150, 0.96 at 210, 0.84 at 300; 384
+//    labels 0.87 and 0.90 at 137 million with 8 and 4.
+//  - the path gradient's arithmetic beside it: 1.03 -> 1.06 ms at 960x540.
+// The winner's pass takes whole chunks of 8 labels, and from 16 labels on the
+// bits (a word of 16 bytes per 128 labels) fit behind the bytes in the room of
+// the 16-bit form.
 bool sgm_narrow(const SgmArgs &a) {
     if ((a.D & 7) || a.D < 16 || a.D > kMaxLabels || a.n_fam > 4 || a.pg || !use_packed(a)) return false;
-    if ((size_t)a.w * a.h * a.D < (size_t)1 << 27) return false;
+    const int pairs = (a.D + 127) / 128, missing = 128 * pairs - a.D;
+    const int may[5] = {0, 0, 40, 96, 128};
+    if (missing > may[pairs]) return false;
+    const size_t large = pairs <= 2 && a.n_dirs < 8 ? (size_t)3 << 26 : (size_t)1 << 27;
+    if ((size_t)a.w * a.h * a.D < large) return false;
     return *std::max_element(a.lut, a.lut + 256) <= 511 && *std::min_element(a.lut, a.lut + 256) >= 0;
 }
 

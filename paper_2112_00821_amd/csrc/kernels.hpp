@@ -85,8 +85,8 @@ struct SgmArgs {
     uint16_t *c3;             // [h][w][3]
 };
 int sgm_paths(int dir, int w, int h);
-// Whether the path costs of these arguments (shape, families, penalties, path
-// gradient) are held narrow in a frame of its own.
+// Whether the path costs of these arguments (shape, families, directions,
+// penalties, path gradient) are held narrow in a frame of its own.
 bool sgm_narrow(const SgmArgs &a);
 // Narrow path costs of one direction of N pixels as 16-bit ones, the n pixels
 // from pixel p0 on: dst[n][D].

@@ -743,6 +743,7 @@ fassmvs_status make_plan(fassmvs_handle *h, const fassmvs_image *ref, const fass
             a.h = L.h;
             a.D = D;
             a.pg = c.sgm_variant == 2;
+            a.n_dirs = c.n_paths;
             a.n_fam = F;
             for (int f = 0; f < F; ++f) a.W[f] = L.W[f];
             std::copy(P.lut, P.lut + 256, a.lut);

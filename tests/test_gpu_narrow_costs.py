@@ -1,8 +1,8 @@
-"""Frames whose path costs are held as 9 bits a label (2^27 labels and more, no
-P2 above 511) against the same frames with every path's costs kept as 16 bits:
-three and four label pairs a lane, three and four families, windows and
-surface-normal shifts.  Path costs, labels and depths are equal, and some
-heights above the matching cost do need their ninth bit."""
+"""Frames whose path costs are held as 9 bits a label (large levels, no P2 above
+511) against the same frames with every path's costs kept as 16 bits: one to
+four label pairs a lane, one to four families, windows and surface-normal
+shifts.  Path costs, labels and depths are equal, and some heights above the
+matching cost do need their ninth bit."""
 import copy
 
 import numpy as np
@@ -12,14 +12,14 @@ import scenegen
 
 pytestmark = pytest.mark.gpu
 
-LABELS = 1 << 27
 
 
 def _frame(planes, families, levels, window, paths, variant):
     wl = copy.deepcopy(scenegen.make_workload("config1"))
     D = families * (window if window else planes)
+    labels = 3 << 26 if paths == 4 and D <= 256 else 1 << 27
     h = 768
-    w = -(-LABELS // (h * D) // 64) * 64 + 64
+    w = -(-labels // (h * D) // 64) * 64 + 64
     grow = lambda im: np.ascontiguousarray(np.tile(im, (-(-h // im.shape[0]), -(-w // im.shape[1])))[:h, :w])
     wl["ref"]["img"] = grow(wl["ref"]["img"])
     for v in wl["views"]:
@@ -28,18 +28,22 @@ def _frame(planes, families, levels, window, paths, variant):
     wl["families"] = [dict(wl["families"][0], count=planes, n=[np.sin(0.05 * i), 0.0, -np.cos(0.05 * i)])
                       for i in range(families)]
     wl["params"].update(n_levels=levels, n_paths=paths, window_labels=window, sgm_variant=variant, p1=50, p2_mode=1)
-    assert LABELS <= w * h * D
+    assert labels <= w * h * D
     return wl, D
 
 
 @pytest.mark.parametrize("planes,families,levels,window,paths,variant", [
-    (136, 2, 1, 0, 8, 0),      # 272 labels: three pairs a lane, the third partly empty
+    (128, 1, 1, 0, 8, 0),      # 128 labels: one pair a lane
+    (128, 1, 1, 0, 4, 0),      # four paths, a larger frame
+    (224, 1, 1, 0, 8, 0),      # 224: two pairs a lane, the second partly empty
+    (144, 2, 1, 0, 8, 0),      # 288 labels: three pairs a lane, the third partly empty
     (96, 4, 1, 0, 8, 0),       # 384: three pairs a lane, full
     (200, 2, 1, 0, 4, 0),      # 400: four pairs a lane
     (128, 4, 1, 0, 8, 0),      # 512: the most labels
-    (32, 3, 2, 40, 8, 1),      # 120: windows and surface-normal shifts of three families
-    (24, 4, 2, 34, 4, 1),      # 136: two pairs a lane
-    (70, 2, 2, 132, 8, 1),     # 264: three
+    (20, 4, 2, 32, 8, 1),      # 128: windows and surface-normal shifts of four families
+    (30, 4, 2, 56, 8, 1),      # 224: two pairs a lane
+    (128, 1, 2, 248, 4, 1),    # 248: the same, one family, a larger frame
+    (76, 2, 2, 144, 8, 1),     # 288: three
     (60, 4, 2, 98, 4, 1),      # 392: four
 ])
 def test_narrow_equals_wide(planes, families, levels, window, paths, variant):
@@ -75,7 +79,7 @@ def test_path_costs_at_any_address():
     """level_map of 9-bit path costs to an odd address (part by part through
     the handle's own memory) gives what it gives to an even one."""
     import paper_2112_00821_amd as fm
-    wl, D = _frame(136, 2, 1, 0, 4, 0)
+    wl, D = _frame(144, 2, 1, 0, 4, 0)
     with fm.Handle(fm.config_from_params(wl["params"], keep_levels=1)) as hd:
         hd.run_frame(wl)
         w, h = hd.level_size(0)

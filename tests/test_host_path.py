@@ -228,7 +228,7 @@ for im in (wl["ref"], *wl["views"]):
     im["img"] = np.tile(im["img"], (9, 7))[:1024, :1088]
 h, w = wl["ref"]["img"].shape
 wl["families"][0]["count"] = D = 128
-wl["params"].update(n_levels=1, n_paths=4, p1=50, p2_mode=1)
+wl["params"].update(n_levels=1, n_paths=8, p1=50, p2_mode=1)
 size = h * w * D * 2
 
 def frame(device):
@@ -295,12 +295,12 @@ for call in ("plain", "pg"):
     hd = frame(0)
     W = np.array([D], np.int32)
     if call == "plain":
-        st = L.fassmvs_stage_sgm(hd.h, w, h, 1, W.ctypes.data, S.vp, None, None, ref.vp, 50, lut.ctypes.data, 4, None,
+        st = L.fassmvs_stage_sgm(hd.h, w, h, 1, W.ctypes.data, S.vp, None, None, ref.vp, 50, lut.ctypes.data, 8, None,
                                  None, wta.vp, c3.vp)
     else:
         delta, n, K, step = np.linspace(1.0, 2.0, D), np.array([0, 0, -1.0]), np.eye(3), np.ones(1)
         st = L.fassmvs_stage_sgm_pg(hd.h, w, h, 1, W.ctypes.data, W.ctypes.data, S.vp, None, ref.vp, 50,
-                                    lut.ctypes.data, 4, delta.ctypes.data, n.ctypes.data, K.ctypes.data,
+                                    lut.ctypes.data, 8, delta.ctypes.data, n.ctypes.data, K.ctypes.data,
                                     step.ctypes.data, None, None, wta.vp, c3.vp)
     assert st == fm.OK
     fake.fake_reset()
@@ -376,4 +376,34 @@ with fm.Handle(fm.default_config(hbm_budget_bytes=n + packed)) as hd:
     assert stage_cost(hd, 640, 480) == fm.OK and quiet(hd, 640, 480)
     assert stage_cost(hd, 640, 480, G=200) == fm.OK, L.fassmvs_last_error(hd.h)
 assert fake.fake_held() == none, (fake.fake_held(), none)
+""")
+
+
+def test_which_frames_hold_nine_bits(child):
+    """The path costs' form by label count, paths and level size (level_map
+    widens nine bits by a kernel and copies sixteen)."""
+    child("""
+import scenegen
+wl = scenegen.make_workload("config1")
+H, M = 1024, 1 << 20
+for labels, families, paths, size, narrow in [
+        (128, 1, 8, 1 << 27, 1), (120, 1, 8, 600 * M, 0), (112, 1, 8, 600 * M, 0), (64, 1, 8, 600 * M, 0),
+        (64, 1, 4, 600 * M, 0), (128, 1, 8, 120 * M, 0), (128, 1, 4, 190 * M, 0), (128, 1, 4, 3 << 26, 1),
+        (136, 1, 8, 600 * M, 0), (208, 2, 8, 400 * M, 0), (216, 1, 8, 1 << 27, 1), (224, 2, 4, 190 * M, 0),
+        (256, 2, 4, 3 << 26, 1), (264, 2, 4, 400 * M, 0), (288, 2, 4, 1 << 27, 1),
+        (392, 4, 8, 1 << 27, 1), (384, 4, 8, 1 << 27, 1), (512, 4, 4, 1 << 27, 1),
+        (127, 1, 8, 400 * M, 0), (132, 1, 8, 400 * M, 0)]:
+    w = -(-size // (H * labels))
+    grow = lambda im: np.tile(im, (-(-H // im.shape[0]), -(-w // im.shape[1])))[:H, :w]
+    f = dict(wl, ref=dict(wl["ref"], img=grow(wl["ref"]["img"])), views=[dict(v, img=grow(v["img"])) for v in wl["views"]],
+             families=[dict(wl["families"][0], count=labels // families)] * families)
+    cfg = fm.config_from_params(dict(wl["params"], n_levels=1, n_paths=paths, p1=50, p2_mode=1), keep_levels=1)
+    with fm.Handle(cfg) as hd:
+        t = hd.submit_frame(f["ref"], f["views"], f["side"], f["K"], f["families"])
+        assert L.fassmvs_poll(hd.h, t, None, None, None, fm.MEM_HOST, -1) == fm.OK
+        n = H * w * labels * 2
+        dst = hd.empty((n,), np.uint8)
+        fake.fake_reset()
+        assert L.fassmvs_level_map(hd.h, 0, 10, dst.ptr, n) == fm.OK
+        assert (fake.fake_calls(b"hipLaunchKernel") == 1) == bool(narrow), (labels, families, paths, size, narrow)
 """)
