@@ -1077,12 +1077,18 @@ SweepArgs sweep_args(fassmvs_handle *h, const FramePlan &P, int l) {
     a.work = (unsigned long long *)h->work_ctr.p;
     // Tile height for the census cost (FASSMVS_SWEEP_ROWS overrides): 64x16
     // tiles where the level is small (more workgroups, smaller unions of
-    // label windows), 64x32 otherwise (fewer halo samples: 1.5 against 1.75
-    // per pixel).  Measured: 640x480 x 168 labels 0.62 ms with 16 rows, 0.67
-    // ms with 32; 960x540 x 128 labels the same; 1920x1080 x 128 labels 5.22
-    // and 4.96 ms.  The same costs either way.
+    // label windows) or where windows of several families move across it (a
+    // tile sweeps the union of every family's), 64x32 otherwise (fewer halo
+    // samples: 1.5 against 1.75 per pixel).  Measured: 640x480 x 168 labels
+    // 0.62 ms with 16 rows, 0.67 ms with 32; 960x540 x 128 labels the same;
+    // 1920x1080 x 128 labels 5.22 and 4.96 ms.  Frames of several families:
+    // 2704x1520, 4 x 96 labels 57.4 and 60.5 ms; 1280x720 13.9 and 14.4;
+    // 1920x1080 29.7 and 29.8, 2 x 128 19.5 and 19.3; a level of 4 x 120
+    // labels without windows, 640x480, 2.53 and 2.45 ms.  The same costs
+    // either way.
     int rows = sweep_rows();
-    if (rows == 0 && c.cost == 0) rows = (double)L.w * L.h * L.D <= 67108864.0 ? 4 : 8;
+    if (rows == 0 && c.cost == 0)
+        rows = (L.F > 1 && L.windows) || (double)L.w * L.h * L.D <= 67108864.0 ? 4 : 8;
     a.rows_per_thread = rows;
     return a;
 }

@@ -189,16 +189,22 @@ hipError_t hipEventQuery(hipEvent_t e) {
 }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
-hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *s) {
-    *grid = *block = dim3(1);
-    *lds = 0;
-    *s = nullptr;
+thread_local struct { dim3 grid, block; size_t lds; hipStream_t s; } config;
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+    config = {grid, block, lds, s};
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *s) {
+    *grid = config.grid;
+    *block = config.block;
+    *lds = config.lds;
+    *s = config.s;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *, dim3, dim3 block, void **, size_t, hipStream_t) {
     Lock lk;
     note("hipLaunchKernel", true);
+    if (block.x == 512) note("512 threads");
     return hipSuccess;
 }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }

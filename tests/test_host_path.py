@@ -407,3 +407,23 @@ for labels, families, paths, size, narrow in [
         assert L.fassmvs_level_map(hd.h, 0, 10, dst.ptr, n) == fm.OK
         assert (fake.fake_calls(b"hipLaunchKernel") == 1) == bool(narrow), (labels, families, paths, size, narrow)
 """)
+
+
+def test_tile_height_by_level(child):
+    """Census sweeps in tiles of 32 rows (workgroups of 512 threads) on large
+    levels, of 16 where windows of several families move across them."""
+    child("""
+import scenegen
+wl = scenegen.make_workload("config2_small")
+h, w = 1024, 1280
+for im in (wl["ref"], *wl["views"]):
+    a = im["img"]
+    im["img"] = np.tile(a, (-(-h // a.shape[0]), -(-w // a.shape[1])))[:h, :w]
+for families, levels, tall in [(1, 2, 1), (3, 2, 0), (3, 1, 1)]:
+    params = dict(wl["params"], n_levels=levels, window_labels=64)
+    fams = [dict(wl["families"][0], count=64)] * families
+    with fm.Handle(fm.config_from_params(params)) as hd:
+        fake.fake_reset()
+        hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], fams)
+        assert fake.fake_calls(b"512 threads") == tall, (families, levels, fake.fake_calls(b"512 threads"))
+""")
