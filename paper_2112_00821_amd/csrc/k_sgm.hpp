@@ -431,6 +431,7 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
     constexpr int PF = KP >= 2 ? 8 : 16;   // steps per block (ring depth): fewer registers for many labels
     constexpr int G2 = PK_G2;
     constexpr int LW = PK_LW;
+    constexpr bool SHIFTS = WIN || SN;   // else every shift is 0 (the path gradient's jump aside)
     const int lane = threadIdx.x & 63;
     // the argument block's scalars as wave-uniform locals (the block may sit
     // in registers, private memory or global memory depending on the caller)
@@ -531,6 +532,7 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             c_off[f] = r.off[f];
+            if (!SHIFTS) continue;
             // (no window is as wide as the bound)
             const int sh = min(max(r.off[f] - r.offp[f] + r.di[f], -2 * kMaxLabels), 2 * kMaxLabels);
             if (NF == 1)
@@ -655,18 +657,14 @@ __device__ __forceinline__ void sgm_pk_path(const SgmArgs a, const int path, con
             }
 #pragma unroll
             for (int k = 0; k < KP; ++k) {
-                Taps tp;
-                if (NF == 1) {
-                    tp = taps_of((word >> 16) + (PG ? jump[0] : 0));
-                } else {
-                    tp = lds.shift[u][fam[k]];
-                    if (PG) {
-                        int jf = jump[0];
+                Taps tp{0, 0u};
+                if (NF > 1 && SHIFTS) tp = lds.shift[u][fam[k]];
+                if (NF == 1 || PG || !SHIFTS) {
+                    int jf = PG ? jump[0] : 0;
 #pragma unroll
-                        for (int f = 1; f < NF; ++f)
-                            if (fam[k] == f) jf = jump[f];
-                        tp = taps_of(tp.step + jf);
-                    }
+                    for (int f = 1; f < NF; ++f)
+                        if (PG && fam[k] == f) jf = jump[f];
+                    tp = taps_of((!SHIFTS ? 0 : NF == 1 ? word >> 16 : tp.step) + jf);
                 }
                 // The taps (j-1, j), (j, j+1), (j+1, j+2) of the pair come from
                 // three aligned words; byte permutes pick them whatever the
