@@ -96,12 +96,15 @@ typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 // every direction buffer with one 16-byte load and adds them as packed 16-bit
 // pairs (the aggregate fits 16 bits by the configuration's bound); argmin and
 // the neighbours' aggregates come from row-level DPP reductions.  Bound by
-// the path costs' bytes (6.3 TB/s at 1920x1080 x 128 labels).  Where the
-// label count is no multiple of 8 the last chunk starts 8 before the end, so
-// that every load stays inside its pixel: the labels it repeats have the same
-// sums.  Rows then start at 2-byte steps and loads are not aligned: 641x479 x
-// 97 labels 0.26 ms with one label a lane, 0.095 ms so.  The narrow forms read
-// 9 bits a label (narrow_sums).
+// the path costs' bytes: 16-bit ones are read at 6.1 TB/s (1920x1080 x 128
+// labels, 8 paths).  Where the label count is no multiple of 8 the last chunk
+// starts 8 before the end, so that every load stays inside its pixel: the
+// labels it repeats have the same sums.  Rows then start at 2-byte steps and
+// loads are not aligned; all directions' are in flight at once (the stage
+// call: 641x479 x 97 labels, 4 paths 308 us with one label a lane, 238 waiting
+// for each direction, 232 so; 33x20 x 31, 8 paths 26.4, 28.0 and 25.6 us).
+// The narrow forms read 9 bits a label (narrow_sums), at 4.8 TB/s: 0.67 ms
+// with 16 bits, 0.55 so.
 typedef unsigned short ushort8_t __attribute__((ext_vector_type(8), aligned(2)));
 typedef uint32_t uint2_t __attribute__((ext_vector_type(2)));
 
@@ -157,10 +160,11 @@ __device__ __forceinline__ void narrow_sums(const SgmArgs &a, size_t p, int c, i
     }
 }
 
-enum WtaForm { kWtaAligned, kWtaUnaligned, kWtaNarrow4, kWtaNarrow8 };
+enum WtaForm { kWtaAligned, kWtaUnaligned4, kWtaUnaligned8, kWtaNarrow4, kWtaNarrow8 };
 template <int NCH, int FORM>
 __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
-    constexpr bool ALIGNED = FORM != kWtaUnaligned;
+    constexpr int UNALIGNED = FORM == kWtaUnaligned4 ? 4 : FORM == kWtaUnaligned8 ? 8 : 0;   // directions
+    constexpr bool ALIGNED = !UNALIGNED;
     constexpr int NARROW = FORM == kWtaNarrow4 ? 4 : FORM == kWtaNarrow8 ? 8 : 0;   // directions
     const int lane = threadIdx.x & 63;
     const int row = lane >> 4, l16 = lane & 15;
@@ -183,17 +187,30 @@ __global__ __launch_bounds__(256) void k_wta16(const SgmArgs a) {
             const int i0c = ALIGNED ? 8 * c : min(8 * c, D - 8);   // the chunk's first label
             ushort2_t s4[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
             if constexpr (NARROW != 0) narrow_sums<NARROW, NCH>(a, pv ? p : N - 1, min(c, nch - 1), j, s4);
+            if constexpr (UNALIGNED != 0) {
+                if (cv) {
+                    ushort8_t v[UNALIGNED];
+#pragma unroll
+                    for (int b = 0; b < UNALIGNED; ++b)
+                        v[b] = __builtin_nontemporal_load((const ushort8_t *)(a.in[b] + p * D + i0c));
+#pragma unroll
+                    for (int b = 0; b < UNALIGNED; ++b) {
+                        const uint4 u = __builtin_bit_cast(uint4, v[b]);
+                        s4[0] = s4[0] + __builtin_bit_cast(ushort2_t, u.x);
+                        s4[1] = s4[1] + __builtin_bit_cast(ushort2_t, u.y);
+                        s4[2] = s4[2] + __builtin_bit_cast(ushort2_t, u.z);
+                        s4[3] = s4[3] + __builtin_bit_cast(ushort2_t, u.w);
+                    }
+                }
+            }
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                if (!NARROW && b < a.n_in && cv) {
+                if (ALIGNED && !NARROW && b < a.n_in && cv) {
                     // each path cost is read once: non-temporal load
                     // through a buffer resource over the whole volume
                     // (32-bit byte offsets), else a plain load
                     uint4 v;
-                    if (!ALIGNED) {
-                        v = __builtin_bit_cast(uint4, __builtin_nontemporal_load(
-                                                          (const ushort8_t *)(a.in[b] + p * D + i0c)));
-                    } else if (rsrc_ok) {
+                    if (rsrc_ok) {
                         const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
                             const_cast<uint16_t *>(a.in[b]), 0, (int)(uint32_t)vol_bytes, 0x00020000);
                         v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
@@ -271,20 +288,24 @@ static void launch_k(const SgmArgs &a, bool win, bool sn, dim3 grid, hipStream_t
 
 static void launch_wta(const SgmArgs &a, hipStream_t s) {
     const size_t N = (size_t)a.w * a.h;
+    const bool four = a.n_in == 4;   // else eight directions
     if (a.D < 8) {
         const dim3 few((unsigned)((N + 63) / 64));
-        if (a.n_in == 4)
+        if (four)
             hipLaunchKernelGGL(k_wta_few<4>, few, dim3(64), 0, s, a);
         else
             hipLaunchKernelGGL(k_wta_few<8>, few, dim3(64), 0, s, a);
         return;
     }
     const dim3 grid((unsigned)std::min<size_t>((N + 15) / 16, 65536)), block(256);
-    const int form = a.narrow ? (a.n_in == 4 ? kWtaNarrow4 : kWtaNarrow8) : (a.D & 7) ? kWtaUnaligned : kWtaAligned;
+    const int form = a.narrow      ? (four ? kWtaNarrow4 : kWtaNarrow8)
+                     : (a.D & 7)   ? (four ? kWtaUnaligned4 : kWtaUnaligned8)
+                                   : kWtaAligned;
 #define FMVS_WTA(N_)                                                                              \
     switch (form) {                                                                              \
         case kWtaAligned: k_wta16<N_, kWtaAligned><<<grid, block, 0, s>>>(a); return;            \
-        case kWtaUnaligned: k_wta16<N_, kWtaUnaligned><<<grid, block, 0, s>>>(a); return;        \
+        case kWtaUnaligned4: k_wta16<N_, kWtaUnaligned4><<<grid, block, 0, s>>>(a); return;      \
+        case kWtaUnaligned8: k_wta16<N_, kWtaUnaligned8><<<grid, block, 0, s>>>(a); return;      \
         case kWtaNarrow4: k_wta16<N_, kWtaNarrow4><<<grid, block, 0, s>>>(a); return;            \
         default: k_wta16<N_, kWtaNarrow8><<<grid, block, 0, s>>>(a); return;                     \
     }
