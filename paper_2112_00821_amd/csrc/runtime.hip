@@ -831,7 +831,10 @@ fassmvs_status weight_table(fassmvs_handle *h, int radius, double beta) {
         }
     fassmvs_status st = ensure(h, h->wtab, t.size() * 8);
     if (st != FASSMVS_OK) return st;
-    HIPCHK(h, hipMemcpy(h->wtab.p, t.data(), t.size() * 8, hipMemcpyHostToDevice), "weight table");
+    // (on the handle's stream: a copy on the null stream fails while another
+    // thread captures a graph, and ends that capture)
+    HIPCHK(h, hipMemcpyAsync(h->wtab.p, t.data(), t.size() * 8, hipMemcpyHostToDevice, h->stream), "weight table");
+    HIPCHK(h, hipStreamSynchronize(h->stream), "weight table");
     h->wtab_at = h->wtab.p;
     h->wtab_radius = radius;
     h->wtab_beta = beta;

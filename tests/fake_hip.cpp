@@ -170,7 +170,12 @@ hipError_t hipMemcpy2DAsync(void *dst, size_t dp, const void *src, size_t sp, si
     for (size_t y = 0; y < h; ++y) queued[s].push_back(Copy{(char *)dst + y * dp, (const char *)src + y * sp, w});
     return hipSuccess;
 }
-hipError_t hipMemcpy(void *dst, const void *src, size_t n, hipMemcpyKind) { std::memcpy(dst, src, n); return hipSuccess; }
+hipError_t hipMemcpy(void *dst, const void *src, size_t n, hipMemcpyKind) {
+    Lock lk;
+    note("hipMemcpy");
+    std::memcpy(dst, src, n);
+    return hipSuccess;
+}
 hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)std::calloc(1, 16); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { std::free((void *)e); return hipSuccess; }

@@ -427,3 +427,16 @@ for families, levels, tall in [(1, 2, 1), (3, 2, 0), (3, 1, 1)]:
         hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], fams)
         assert fake.fake_calls(b"512 threads") == tall, (families, levels, fake.fake_calls(b"512 threads"))
 """)
+
+
+def test_frames_leave_the_null_stream_alone(child):
+    """A copy on the null stream fails while any thread captures a graph (and
+    ends that capture): a first frame makes none."""
+    child("""
+import scenegen
+wl = scenegen.make_workload("config1")
+with fm.Handle(fm.config_from_params(wl["params"])) as hd:
+    hd.run_frame(wl)
+    hd.run_batch([wl, wl])
+assert fake.fake_calls(b"hipMemcpy") == 0
+""")
