@@ -10,8 +10,8 @@
 //
 // A mover belongs to one handle (or server) and is used under its lock; slots
 // and helper threads are made on first use and given back with it.  Helpers
-// sleep between transfers.  Without memory for the slots, or threads, the
-// copies still happen (by the runtime, or by the calling thread alone).
+// sleep between transfers.  Without free CPUs, memory for the slots, or
+// threads, the runtime copies.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -52,6 +52,17 @@ struct DeviceRanges {
     }
 };
 
+// A thread of the process inside a call that copies, or waits to.
+struct HostCaller {
+    HostCaller() { now().fetch_add(1); }
+    ~HostCaller() { now().fetch_sub(1); }
+    HostCaller(const HostCaller &) = delete;
+    static std::atomic<int> &now() {
+        static std::atomic<int> n{0};
+        return n;
+    }
+};
+
 class HostMover {
 public:
     HostMover() = default;
@@ -69,17 +80,16 @@ public:
         if (pin_) hipHostFree(pin_);
     }
 
-    // Copy pieces between host buffers, shared with the helpers where that
-    // is worth waking them.
-    void copy(const std::vector<HostPiece> &pieces) {
+    // Copy pieces between host buffers with helpers, where that is worth
+    // waking them and CPUs are free; false: nothing is copied.
+    bool copy(const std::vector<HostPiece> &pieces) {
         size_t total = 0;
         for (auto &p : pieces) total += p.bytes * p.rows;
-        if (total < kShare) {
-            for (auto &p : pieces) p.copy();
-            return;
-        }
+        if (total < kShare) return false;
         Session s(*this);
+        if (s.taken == 0) return false;
         share(pieces.data(), pieces.size());
+        return true;
     }
 
     // Device ranges to host memory, after the work already on the stream;
@@ -89,14 +99,13 @@ public:
     hipError_t to_host(const DeviceRanges &ranges, hipStream_t stream) {
         if (ranges.n == 0) return hipSuccess;
         DeviceRanges staged, direct;
-        const bool slotted = split(ranges, staged, direct) && slots();
-        const DeviceRanges &whole = slotted ? direct : ranges;
-        hipError_t e = hipSuccess;
-        for (size_t i = 0; i < whole.n && e == hipSuccess; ++i)
-            e = hipMemcpyAsync(whole.r[i].dst, whole.r[i].src, whole.r[i].bytes, hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess && slotted) e = through_slots(staged, stream);
-        const hipError_t es = hipStreamSynchronize(stream);
-        return e == hipSuccess ? es : e;
+        if (!split(ranges, staged, direct)) return whole(ranges, stream);
+        Session s(*this);
+        if (s.taken == 0 || !slots()) return whole(ranges, stream);
+        hipError_t e = whole(direct, stream);
+        if (e == hipSuccess) e = through_slots(staged, stream);
+        if (e != hipSuccess) (void)hipStreamSynchronize(stream);
+        return e;
     }
 
     // What the first to_host of these ranges (of so many bytes) would make,
@@ -106,7 +115,7 @@ public:
         if (!pin_ && split(ranges, staged, direct)) prepare(kShare);
     }
     void prepare(size_t bytes) {
-        if (!pin_ && bytes >= kShare && slots()) helpers();
+        if (!pin_ && bytes >= kShare && free_cpus() >= kLeast && slots()) helpers();
     }
 
     static constexpr size_t kPiece = 128 << 10;
@@ -116,6 +125,22 @@ private:
     // change nothing); below 1 MB a transfer is not worth waking helpers
     static constexpr size_t kSlot = 2 << 20, kSlots = 2, kShare = 1 << 20;
     static constexpr int kHelpers = 5;   // 3: 37 GB/s, 5: 39, 7: the same
+    // Helpers wait actively for their pieces, so they are for CPUs that are
+    // free: kCallerCpus are left to each thread that polls, copies or submits
+    // now (its own, the runtime's and the program's work), and fewer than
+    // kLeast helpers are not worth the slots: without them the runtime copies.
+    // 640x480 frames a second of 1, 2, 4, 8 and 14 threads with a handle each,
+    // 16 CPUs: always with helpers 1410, 2100, 2560, 1490 and 1770, never 1190,
+    // 1900, 3310, 3950 and 4210, by this rule 1465, 2350, 3110, 3775 and 4160.
+    static constexpr int kLeast = 2, kCallerCpus = 5;
+    static int free_cpus() {
+        return (int)std::thread::hardware_concurrency() - kCallerCpus * std::max(1, HostCaller::now().load());
+    }
+    // Helpers of running sessions, over all movers.
+    static std::atomic<int> &in_use() {
+        static std::atomic<int> n{0};
+        return n;
+    }
 
     uint8_t *slot(size_t k) { return pin_ + k * kSlot; }
 
@@ -144,7 +169,18 @@ private:
         return total >= kShare;
     }
 
-    // (after an error copies into the slots may still run)
+    // One copy each, by the runtime.
+    static hipError_t whole(const DeviceRanges &ranges, hipStream_t stream) {
+        if (ranges.n == 0) return hipSuccess;
+        hipError_t e = hipSuccess;
+        for (size_t i = 0; i < ranges.n && e == hipSuccess; ++i)
+            e = hipMemcpyAsync(ranges.r[i].dst, ranges.r[i].src, ranges.r[i].bytes, hipMemcpyDeviceToHost, stream);
+        const hipError_t es = hipStreamSynchronize(stream);
+        return e == hipSuccess ? es : e;
+    }
+
+    // With the helpers of a session; after an error copies into the slots may
+    // still run.
     hipError_t through_slots(const DeviceRanges &ranges, hipStream_t stream) {
         DeviceRange in[kSlots];   // what each slot receives
         size_t at = 0, off = 0, sent = 0;
@@ -162,8 +198,6 @@ private:
         };
         hipError_t e = hipSuccess;
         while (e == hipSuccess && sent < kSlots && at < ranges.n) e = send();
-        if (e != hipSuccess) return e;
-        Session s(*this);
         for (size_t i = 0; i < sent && e == hipSuccess; ++i) {
             const size_t k = i % kSlots;
             if ((e = hipEventSynchronize(events_[k])) != hipSuccess) break;
@@ -196,9 +230,8 @@ private:
     }
 
     void helpers() {
-        const int want = std::min(kHelpers, (int)std::thread::hardware_concurrency() / 2);
         try {
-            while ((int)threads_.size() < want) threads_.emplace_back([this] { help(); });
+            while ((int)threads_.size() < kHelpers) threads_.emplace_back([this, i = (int)threads_.size()] { help(i); });
         } catch (...) {   // no thread, or no memory for one: with fewer
         }
     }
@@ -206,15 +239,31 @@ private:
     // Helpers take part between a session's start and its end.
     struct Session {
         HostMover &m;
+        int taken = 0;
         explicit Session(HostMover &mm) : m(mm) {
+            int n = in_use().load();
+            do {
+                taken = std::min(kHelpers, free_cpus() - n);
+                if (taken < kLeast) {
+                    taken = 0;
+                    return;
+                }
+            } while (!in_use().compare_exchange_weak(n, n + taken));
             m.helpers();
+            const int made = (int)m.threads_.size() < kLeast ? 0 : std::min(taken, (int)m.threads_.size());
+            in_use().fetch_sub(taken - made);
+            if ((taken = made) == 0) return;
             {
                 std::lock_guard<std::mutex> lk(m.m_);
-                m.active_.store(true);
+                m.active_.store(taken);
             }
             m.cv_.notify_all();
         }
-        ~Session() { m.active_.store(false); }
+        Session(const Session &) = delete;
+        ~Session() {
+            m.active_.store(0);
+            in_use().fetch_sub(taken);
+        }
     };
 
     // One batch: every piece copied when this returns.  state_ holds the
@@ -244,13 +293,13 @@ private:
         }
     }
 
-    void help() {
+    void help(int i) {   // of the session's taken helpers, if i is one
         std::unique_lock<std::mutex> lk(m_);
         for (;;) {
-            cv_.wait(lk, [this] { return stop_ || active_.load(); });
+            cv_.wait(lk, [this, i] { return stop_ || i < active_.load(); });
             if (stop_) return;
             lk.unlock();
-            while (active_.load()) {
+            while (i < active_.load()) {
                 work();
                 pause();
             }
@@ -266,7 +315,7 @@ private:
     std::mutex m_;
     std::condition_variable cv_;
     bool stop_ = false;
-    std::atomic<bool> active_{false};
+    std::atomic<int> active_{0};   // helpers of the running session
     std::atomic<uint64_t> state_{0};
     std::atomic<const HostPiece *> pieces_{nullptr};
     std::atomic<uint32_t> count_{0};

@@ -1248,6 +1248,7 @@ fassmvs_status upload_frame(fassmvs_handle *h, HostMover &mover, const FramePlan
     const size_t N0 = (size_t)P.w * P.h;
     Timer t(h, ST_UPLOAD);
     uint8_t *pin = (uint8_t *)h->pin;
+    bool staged = false;   // the images are in the staging already
     if (mem_kind == FASSMVS_MEM_HOST) {
         std::vector<HostPiece> pieces;
         const size_t band = std::max<size_t>(1, HostMover::kPiece / P.w);   // rows of a piece
@@ -1257,13 +1258,16 @@ fassmvs_status upload_frame(fassmvs_handle *h, HostMover &mover, const FramePlan
                 pieces.push_back({pin + N0 * i + y * P.w, im.pixels + y * im.stride, (size_t)P.w,
                                   std::min(band, P.h - y), (size_t)P.w, (size_t)im.stride});
         }
-        mover.copy(pieces);
+        staged = mover.copy(pieces);
     }
     for (int i = 0; i <= P.n_views; ++i) {
         const fassmvs_image &im = i == 0 ? *ref : views[i - 1];
         uint8_t *dst = (uint8_t *)h->pyr[i].p;
         if (mem_kind == FASSMVS_MEM_HOST) {
             uint8_t *stg = pin + N0 * i;
+            if (!staged)
+                for (int y = 0; y < P.h; ++y)
+                    std::memcpy(stg + (size_t)y * P.w, im.pixels + (size_t)y * im.stride, P.w);
             HIPCHK(h, hipMemcpyAsync(dst, stg, N0, hipMemcpyHostToDevice, h->stream), "image upload");
         } else if (h->prebuilt) {
             HIPCHK(h, hipMemcpyAsync(dst, im.pixels, level_offset(P, P.n_levels), hipMemcpyDeviceToDevice, h->stream),
@@ -1740,6 +1744,7 @@ fassmvs_status submit_frame_locked(fassmvs_handle *h, const fassmvs_image *ref, 
                                    const int8_t *view_side, int32_t n_views, const double K[9],
                                    const fassmvs_plane_family *families, int32_t n_families, int32_t mem_kind,
                                    uint64_t *ticket) {
+    const HostCaller caller;
     if (h->latched) return FASSMVS_EDEVICE;
     if (h->busy || h->batch_busy) return fail(h, FASSMVS_EBUSY, "a frame is in flight; poll it first");
     if (!ticket) return fail(h, FASSMVS_EINVAL, "null ticket");
@@ -1998,6 +2003,7 @@ fassmvs_status fassmvs_submit_frame_range(fassmvs_handle *h, const fassmvs_image
 fassmvs_status fassmvs_submit_batch(fassmvs_handle *h, const fassmvs_frame *frames, int32_t n_frames, int32_t mem_kind,
                                     uint64_t *ticket) {
     if (!h) return FASSMVS_EINVAL;
+    const HostCaller caller;
     std::lock_guard<std::mutex> lk(h->mu);
     if (h->latched) return FASSMVS_EDEVICE;
     if (h->busy || h->batch_busy) return fail(h, FASSMVS_EBUSY, "a frame or batch is in flight; poll it first");
@@ -2166,6 +2172,7 @@ fassmvs_status fassmvs_submit_batch(fassmvs_handle *h, const fassmvs_frame *fram
 fassmvs_status fassmvs_poll_batch(fassmvs_handle *h, uint64_t ticket, int32_t index, float *depth, float *normal,
                                   float *confidence, int32_t mem_kind, int32_t wait_ms) {
     if (!h) return FASSMVS_EINVAL;
+    const HostCaller caller;
     std::lock_guard<std::mutex> lk(h->mu);
     if (h->latched) return FASSMVS_EDEVICE;
     if (ticket == 0 || ticket != h->batch_ticket) return fail(h, FASSMVS_ENOTFOUND, "unknown batch ticket");
@@ -2318,6 +2325,7 @@ extern "C" {
 fassmvs_status fassmvs_poll(fassmvs_handle *h, uint64_t ticket, float *depth, float *normal, float *confidence,
                             int32_t mem_kind, int32_t wait_ms) {
     if (!h) return FASSMVS_EINVAL;
+    const HostCaller caller;
     std::lock_guard<std::mutex> lk(h->mu);
     if (h->latched) return FASSMVS_EDEVICE;
     if (!h->busy || ticket != h->ticket) return fail(h, FASSMVS_ENOTFOUND, "unknown ticket");
@@ -2581,6 +2589,7 @@ fassmvs_status fassmvs_device_free(fassmvs_handle *h, void *ptr) {
 fassmvs_status fassmvs_memcpy(fassmvs_handle *h, void *dst, const void *src, size_t bytes, int32_t kind) {
     if (!h || (!dst && bytes) || (!src && bytes)) return FASSMVS_EINVAL;
     if (kind < 0 || kind > 2) return FASSMVS_EINVAL;
+    const HostCaller caller;
     std::lock_guard<std::mutex> lk(h->mu);
     hipSetDevice(h->cfg.device);
     if (bytes == 0) return FASSMVS_OK;

@@ -604,6 +604,7 @@ fassmvs_status fassmvs_server_next(fassmvs_server *s, int32_t wait_ms, fassmvs_s
 fassmvs_status fassmvs_server_fetch(fassmvs_server *s, uint64_t request_id, float *depth, float *normal,
                                     float *confidence, int32_t mem_kind) {
     if (!s) return FASSMVS_EINVAL;
+    const fmvs::HostCaller caller;
     if (mem_kind != FASSMVS_MEM_HOST && mem_kind != FASSMVS_MEM_DEVICE) return sfail(s, FASSMVS_EINVAL, "bad mem_kind");
     Result r;
     {

@@ -92,6 +92,11 @@ void *operator new(size_t n) {
 void operator delete(void *p) noexcept { std::free(p); }
 void operator delete(void *p, size_t) noexcept { std::free(p); }
 
+static std::atomic<unsigned> cpus{16};
+// std::thread::hardware_concurrency
+extern "C" unsigned fake_hardware_concurrency() __asm__("_ZNSt6thread20hardware_concurrencyEv");
+unsigned fake_hardware_concurrency() { return cpus; }
+
 extern "C" {
 // what the tests read and set
 long fake_calls(const char *name) {
@@ -110,6 +115,7 @@ size_t fake_peak() { return peak; }
 void fake_limit(size_t bytes) { limit = bytes; }
 void fake_fail_copy(long after) { fail_copy = after; }
 void fake_not_ready(long n) { not_ready = n; }
+void fake_cpus(unsigned n) { cpus = n; }
 void fake_no_memory(int on) { no_memory = on != 0; }   // host allocations (operator new) fail
 void fake_expect_device(int d) { expected = d; }
 int fake_on_wrong_device() { return on_wrong; }

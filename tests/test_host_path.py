@@ -21,6 +21,7 @@ fake.fake_limit.argtypes = [C.c_size_t]
 fake.fake_fail_copy.argtypes = [C.c_long]
 fake.fake_pinned.restype = C.c_void_p
 fake.fake_pinned.argtypes = [C.c_size_t]
+fake.fake_not_ready.argtypes = [C.c_long]
 sys.path[:0] = [{root!r}, {root!r} + "/tests"]
 import numpy as np
 import paper_2112_00821_amd as fm
@@ -439,4 +440,46 @@ with fm.Handle(fm.config_from_params(wl["params"])) as hd:
     hd.run_frame(wl)
     hd.run_batch([wl, wl])
 assert fake.fake_calls(b"hipMemcpy") == 0
+""")
+
+
+def test_helpers_only_for_free_cpus(child):
+    """Helper threads wait actively: a transfer takes them (and the slots, three
+    chunks here) only while CPUs are free beside the threads inside calls, and
+    else goes the runtime's way, in one copy."""
+    child("""
+import threading, time, scenegen
+n = 5 * MB
+out = np.zeros(n, np.uint8)
+wl = scenegen.make_workload("config1")
+
+def copies(h, d):
+    fake.fake_reset()
+    assert L.fassmvs_memcpy(h.h, out.ctypes.data, d.ptr, n, 1) == fm.OK
+    return fake.fake_calls(b"hipMemcpyAsync")
+
+def frame():
+    hd = fm.Handle(fm.config_from_params(wl["params"]))
+    return hd, hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], wl["families"])
+
+with fm.Handle(fm.default_config()) as h:
+    d = h.upload(np.random.default_rng(0).integers(0, 256, n, dtype=np.uint8))
+    for cpus, expect in ((16, 3), (8, 3), (4, 1), (1, 1), (16, 3)):
+        fake.fake_cpus(cpus)
+        assert copies(h, d) == expect, cpus
+    for others, expect in ((1, 3), (2, 1), (6, 1)):
+        frames = [frame() for _ in range(others)]
+        fake.fake_not_ready(1 << 40)
+        ts = [threading.Thread(target=lambda f=f: L.fassmvs_poll(f[0].h, f[1], None, None, None, fm.MEM_HOST, 1000))
+              for f in frames]
+        for t in ts:
+            t.start()
+            time.sleep(0.3)
+        got = copies(h, d)
+        for t in ts:
+            t.join()
+        fake.fake_not_ready(0)
+        assert got == expect, (others, got)
+    assert copies(h, d) == 3
+    assert np.array_equal(out, d.numpy())
 """)
