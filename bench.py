@@ -38,8 +38,9 @@ SGM_ALG_BYTES = 12.0
 # bytes of this design per (pixel, hypothesis): S read by each of the 8
 # direction walks (8 x 1 B), each direction's uint16 path costs written once
 # and read once by the streaming winner-takes-all (2 x 8 x 2 B); levels of
-# 2^27 labels and more hold 9 bits in place of the uint16, and the
-# winner-takes-all reads S once more (8 + 2 x 8 x 9 / 8 + 1 B)
+# 2^27 labels and more, 128 or 384 a pixel in these workloads, hold 9 bits in
+# place of the uint16, and the winner-takes-all reads S once more
+# (8 + 2 x 8 x 9 / 8 + 1 B)
 SGM_DESIGN_BYTES = 40.0
 SGM_DESIGN_BYTES_NARROW = 27.0
 

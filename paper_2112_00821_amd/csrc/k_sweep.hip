@@ -48,8 +48,11 @@ int sweep_chunks(const SweepArgs &a, int tiles, int rpt, double waves) {
     const int full = (int)std::min(std::ceil(waves / per_chunk), 1e6);
     const int half = (int)std::min(std::ceil(0.5 * waves / per_chunk), 1e6);
     const int n = std::max(1, std::max(std::min(full, runs), std::min(half, words)));
-    // whole words of four labels each: 31 chunks of 32 words would leave one
-    // of twice the length (480x270 x 128 labels: 0.39 ms, 0.35 ms with 32)
+    // equal chunks, of whole words of four labels: 31 chunks of 32 words would
+    // leave one of twice the length (480x270 x 128 labels: 0.39 ms, 0.35 ms
+    // with 32).  The count is rounded up to that, so between n and twice n (17
+    // chunks of 32 words become 32).  On levels with windows the kernel deals
+    // out the words of a tile's window union, which are D's or more.
     const int len = std::max(1, words / n);
     return (words + len - 1) / len;
 }

@@ -48,7 +48,7 @@ namespace fmvs {
 // 32-bit byte offsets (2^30 texels).  A stage call packed, packing included,
 // and in bytes: 160x120, 2 views, 32 labels, 5x5 51 and 47 us; 640x480, 2, 64,
 // 9x7 238 and 251; 1920x1080, 4, 128, 9x7 4.09 and 4.74 ms.
-enum SweepSource { kPacked, kWarped, kBytes };
+enum SweepSource : int { kPacked, kWarped, kBytes };
 
 namespace {
 constexpr int TW = 64;       // tile width: a wavefront's row
@@ -111,7 +111,7 @@ struct SweepTile {
 // What a wavefront holds of the samples it has requested: the packed 2x2
 // texels (four bytes each in a register of its own; the value itself, from
 // pre-warped views) and the fractions.
-template <int NST, SweepSource SRC>
+template <int NST, int SRC>
 struct Pending {
     uint32_t tex[NST][SRC == kBytes ? 4 : 1];
     float ax[NST], ay[NST];
@@ -129,10 +129,11 @@ __device__ __forceinline__ int ncc_cost_exact(double cov, double p) {
 }
 // The correctly rounded square root and division (about 60 instructions, half
 // of a 5x5 window's sums) decide the cost only where
-// 255 (1 - rho) + 0.5 lies next to a whole number: rho in float (two
-// conversions, the reciprocal square root within an ulp and a product: 4 x
-// 2^-24 of it) is off by at most 1e-4 in that number, so further from one
-// its floor is the same, and only the remaining pixels take them.
+// 255 (1 - rho) + 0.5 lies next to a whole number: rho in float is off by at
+// most 4.5 x 2^-24 of it (the covariance's conversion 1, the product's under
+// the root 1/2, the reciprocal square root within an ulp 2, the product 1),
+// 6.9e-5 of 255, and that number's own rounding adds 0.8e-5, so 1e-4 further
+// from a whole number its floor is the same, and only the remaining pixels take them.
 // 1920x1080, 3 views, 128 labels, 5x5, three levels: 8.6 ms with them for
 // every pixel and a rolled row loop, 5.1 ms so.
 __device__ __forceinline__ int ncc_finish(int sA_i, int vA_i, double sB, double sBB, double sAB, double n) {
@@ -159,7 +160,7 @@ __device__ __forceinline__ int xcd_logical(int b, int nb) {
 
 // One workgroup's share of the sweep of one frame: logical = tile *
 // n_chunks + chunk.
-template <int CW, int CH, int NW, SweepSource SRC, int COST>
+template <int CW, int CH, int NW, int SRC, int COST>
 __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
     constexpr bool WARPED = SRC == kWarped;
     typedef SweepTile<CW, CH, NW> T;
@@ -639,7 +640,7 @@ __device__ __forceinline__ void sweep_block(ArgsC &a, const int logical) {
     }
 }
 
-template <int CW, int CH, int NW, SweepSource SRC, int COST>
+template <int CW, int CH, int NW, int SRC, int COST>
 __global__ __launch_bounds__(64 * NW, SRC == kBytes ? 2 : kSweepWaves) void k_sweep(const SweepArgs) {
     // the arguments, in place
     ArgsC &a = *(ArgsC *)__builtin_amdgcn_kernarg_segment_ptr();
