@@ -348,9 +348,10 @@ void collect_timers(fassmvs_handle *h) {
     h->frame_t0 = nullptr;
 }
 
-// Sweep tuning knob, read at every launch: FASSMVS_SWEEP_ROWS = 4 or 8 rows
-// per thread (tile 64x16 or 64x32).  Unset, the launcher picks 8 for census
-// and 4 for NCC.  It changes the schedule only, never the result.
+// Sweep tuning knob, read at every launch: FASSMVS_SWEEP_ROWS = 4 or 8
+// wavefronts of four rows per tile (64x16 or 64x32).  Unset, frames choose by
+// level (sweep_args), the stage calls take 8 for census and 4 for NCC.  It
+// changes the schedule only, never the result.
 int sweep_rows() {
     const char *e = std::getenv("FASSMVS_SWEEP_ROWS");
     const int r = e ? std::atoi(e) : 0;
