@@ -2387,6 +2387,10 @@ void fassmvs_destroy(fassmvs_handle *h) {
         release(h->work_ctr);
         release(h->sbar);
         release(h->packed);
+        release(h->post_tmp);
+        release(h->post_m0);
+        release(h->post_m1);
+        release(h->post_hits);
         release(h->wtab);
         for (auto &b : h->sgmbuf) release(b);
         for (auto &L : h->lb) {

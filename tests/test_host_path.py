@@ -483,3 +483,30 @@ with fm.Handle(fm.default_config()) as h:
     assert copies(h, d) == 3
     assert np.array_equal(out, d.numpy())
 """)
+
+
+def test_destroy_gives_all_memory_back(child):
+    """Frames (with the DoG filter), a batch, the filters and the stage calls:
+    nothing of the handle is left on the device or page-locked."""
+    child(COST + """
+import scenegen
+wl = scenegen.make_workload("config1")
+h, w = wl["ref"]["img"].shape
+none = fake.fake_held()
+locked = lambda: fake.fake_calls(b"hipHostMalloc") - fake.fake_calls(b"hipHostFree")
+before = locked()
+with fm.Handle(fm.config_from_params(wl["params"], dog_filter=1, keep_levels=1)) as hd:
+    hd.run_frame(wl)
+    hd.run_batch([wl, wl])
+    assert stage_cost(hd, 320, 240) == fm.OK
+    img, d = hd.empty((h, w), np.uint8), hd.empty((h, w), np.float32)
+    hd.filter_dog(img, d, None, None)
+    K = np.array(wl["K"], float)
+    nb = (C.c_void_p * 1)(d.ptr)
+    R, t = np.eye(3), np.zeros(3)
+    assert L.fassmvs_filter_geometric(hd.h, w, h, K.ctypes.data, d.vp, None, None, 1, nb, R.ctypes.data, t.ctypes.data,
+                                      10.0, 0, None, None) == fm.OK
+    del img, d
+assert fake.fake_held() == none, fake.fake_held() - none
+assert locked() == before
+""")
