@@ -88,6 +88,7 @@ public:
         if (total < kShare) return false;
         Session s(*this);
         if (s.taken == 0) return false;
+        s.wake();
         share(pieces.data(), pieces.size());
         return true;
     }
@@ -103,7 +104,7 @@ public:
         Session s(*this);
         if (s.taken == 0 || !slots()) return whole(ranges, stream);
         hipError_t e = whole(direct, stream);
-        if (e == hipSuccess) e = through_slots(staged, stream);
+        if (e == hipSuccess) e = through_slots(staged, stream, s);
         if (e != hipSuccess) (void)hipStreamSynchronize(stream);
         return e;
     }
@@ -133,9 +134,7 @@ private:
     // 16 CPUs: always with helpers 1410, 2100, 2560, 1490 and 1770, never 1190,
     // 1900, 3310, 3950 and 4210, by this rule 1465, 2350, 3110, 3775 and 4160.
     static constexpr int kLeast = 2, kCallerCpus = 5;
-    static int free_cpus() {
-        return (int)std::thread::hardware_concurrency() - kCallerCpus * std::max(1, HostCaller::now().load());
-    }
+    int free_cpus() const { return cpus_ - kCallerCpus * std::max(1, HostCaller::now().load()); }
     // Helpers of running sessions, over all movers.
     static std::atomic<int> &in_use() {
         static std::atomic<int> n{0};
@@ -179,9 +178,11 @@ private:
         return e == hipSuccess ? es : e;
     }
 
+    struct Session;
+
     // With the helpers of a session; after an error copies into the slots may
     // still run.
-    hipError_t through_slots(const DeviceRanges &ranges, hipStream_t stream) {
+    hipError_t through_slots(const DeviceRanges &ranges, hipStream_t stream, Session &s) {
         DeviceRange in[kSlots];   // what each slot receives
         size_t at = 0, off = 0, sent = 0;
         auto send = [&] {   // the next chunk
@@ -198,6 +199,7 @@ private:
         };
         hipError_t e = hipSuccess;
         while (e == hipSuccess && sent < kSlots && at < ranges.n) e = send();
+        s.wake();   // (while the first chunk is on its way)
         for (size_t i = 0; i < sent && e == hipSuccess; ++i) {
             const size_t k = i % kSlots;
             if ((e = hipEventSynchronize(events_[k])) != hipSuccess) break;
@@ -236,14 +238,14 @@ private:
         }
     }
 
-    // Helpers take part between a session's start and its end.
+    // Helpers are a session's from its start and take part from wake() on.
     struct Session {
         HostMover &m;
         int taken = 0;
         explicit Session(HostMover &mm) : m(mm) {
             int n = in_use().load();
             do {
-                taken = std::min(kHelpers, free_cpus() - n);
+                taken = std::min(kHelpers, m.free_cpus() - n);
                 if (taken < kLeast) {
                     taken = 0;
                     return;
@@ -252,7 +254,9 @@ private:
             m.helpers();
             const int made = (int)m.threads_.size() < kLeast ? 0 : std::min(taken, (int)m.threads_.size());
             in_use().fetch_sub(taken - made);
-            if ((taken = made) == 0) return;
+            taken = made;
+        }
+        void wake() {
             {
                 std::lock_guard<std::mutex> lk(m.m_);
                 m.active_.store(taken);
@@ -309,6 +313,7 @@ private:
 
     static void pause() { __builtin_ia32_pause(); }
 
+    const int cpus_ = (int)std::thread::hardware_concurrency();   // (a call of some microseconds)
     uint8_t *pin_ = nullptr;
     hipEvent_t events_[kSlots] = {};
     std::vector<std::thread> threads_;

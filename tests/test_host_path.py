@@ -462,11 +462,15 @@ def frame():
     hd = fm.Handle(fm.config_from_params(wl["params"]))
     return hd, hd.submit_frame(wl["ref"], wl["views"], wl["side"], wl["K"], wl["families"])
 
+a = np.random.default_rng(0).integers(0, 256, n, dtype=np.uint8)
+for cpus, expect in ((16, 3), (8, 3), (4, 1), (1, 1)):
+    fake.fake_cpus(cpus)
+    with fm.Handle(fm.default_config()) as h:
+        assert copies(h, h.upload(a)) == expect, cpus
+        assert np.array_equal(out, a)
+fake.fake_cpus(16)
 with fm.Handle(fm.default_config()) as h:
-    d = h.upload(np.random.default_rng(0).integers(0, 256, n, dtype=np.uint8))
-    for cpus, expect in ((16, 3), (8, 3), (4, 1), (1, 1), (16, 3)):
-        fake.fake_cpus(cpus)
-        assert copies(h, d) == expect, cpus
+    d = h.upload(a)
     for others, expect in ((1, 3), (2, 1), (6, 1)):
         frames = [frame() for _ in range(others)]
         fake.fake_not_ready(1 << 40)
