@@ -371,7 +371,8 @@ static bool use_packed(const SgmArgs &a) {
 //    six processes a side (which differ by up to 1.2): 64 labels 1.15, 96 1.28,
 //    112 1.21, 120 1.02, 128 0.95; two pairs a lane 136 1.11, 168 1.05, 192
 //    1.09, 208 1.02, 216 0.92, 256 0.95; three 264 1.03, 288 1.00, 304 0.94,
-//    384 0.87; four 392 0.89, 512 0.78.
+//    384 0.87; four 392 0.89, 512 0.78.  4 paths: 64 1.08, 112 1.10, 120 0.92,
+//    128 0.96; 136 1.05, 192 1.07, 200 0.92, 216 0.87; 264 0.96.
 //  - the level's size: 128 labels, 8 paths 0.99 at 109 million labels, 0.97 at
 //    150, 0.82 at 300; 4 paths 1.01 at 150, 0.96 at 210, 0.84 at 300; 384
 //    labels 0.87 and 0.90 at 137 million with 8 and 4.
@@ -382,8 +383,8 @@ static bool use_packed(const SgmArgs &a) {
 bool sgm_narrow(const SgmArgs &a) {
     if ((a.D & 7) || a.D < 16 || a.D > kMaxLabels || a.n_fam > 4 || a.pg || !use_packed(a)) return false;
     const int pairs = (a.D + 127) / 128, missing = 128 * pairs - a.D;
-    const int may[5] = {0, 0, 40, 96, 128};
-    if (missing > may[pairs]) return false;
+    const int may[2][5] = {{0, 8, 56, 120, 128}, {0, 0, 40, 96, 128}};
+    if (missing > may[a.n_dirs == 8][pairs]) return false;
     const size_t large = pairs <= 2 && a.n_dirs < 8 ? (size_t)3 << 26 : (size_t)1 << 27;
     if ((size_t)a.w * a.h * a.D < large) return false;
     return *std::max_element(a.lut, a.lut + 256) <= 511 && *std::min_element(a.lut, a.lut + 256) >= 0;

@@ -35,6 +35,9 @@ def _frame(planes, families, levels, window, paths, variant):
 @pytest.mark.parametrize("planes,families,levels,window,paths,variant", [
     (128, 1, 1, 0, 8, 0),      # 128 labels: one pair a lane
     (128, 1, 1, 0, 4, 0),      # four paths, a larger frame
+    (120, 1, 1, 0, 4, 0),      # 120: the pair's last lanes empty
+    (200, 1, 1, 0, 4, 0),      # 200
+    (132, 2, 1, 0, 4, 0),      # 264
     (224, 1, 1, 0, 8, 0),      # 224: two pairs a lane, the second partly empty
     (144, 2, 1, 0, 8, 0),      # 288 labels: three pairs a lane, the third partly empty
     (96, 4, 1, 0, 8, 0),       # 384: three pairs a lane, full

@@ -391,7 +391,8 @@ for labels, families, paths, size, narrow in [
         (128, 1, 8, 1 << 27, 1), (120, 1, 8, 600 * M, 0), (112, 1, 8, 600 * M, 0), (64, 1, 8, 600 * M, 0),
         (64, 1, 4, 600 * M, 0), (128, 1, 8, 120 * M, 0), (128, 1, 4, 190 * M, 0), (128, 1, 4, 3 << 26, 1),
         (136, 1, 8, 600 * M, 0), (208, 2, 8, 400 * M, 0), (216, 1, 8, 1 << 27, 1), (224, 2, 4, 190 * M, 0),
-        (256, 2, 4, 3 << 26, 1), (264, 2, 4, 400 * M, 0), (288, 2, 4, 1 << 27, 1),
+        (256, 2, 4, 3 << 26, 1), (264, 2, 8, 400 * M, 0), (264, 2, 4, 1 << 27, 1), (120, 1, 4, 3 << 26, 1), (112, 1, 4, 600 * M, 0),
+        (192, 1, 4, 400 * M, 0), (200, 1, 4, 3 << 26, 1), (200, 1, 8, 400 * M, 0), (288, 2, 4, 1 << 27, 1),
         (392, 4, 8, 1 << 27, 1), (384, 4, 8, 1 << 27, 1), (512, 4, 4, 1 << 27, 1),
         (127, 1, 8, 400 * M, 0), (132, 1, 8, 400 * M, 0)]:
     w = -(-size // (H * labels))
